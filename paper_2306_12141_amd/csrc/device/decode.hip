@@ -38,6 +38,7 @@
 #include <atomic>
 
 #include "decode_core.hpp"
+#include "few.hpp"
 
 namespace recoil {
 
@@ -151,7 +152,9 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
         // workgroups would not reach every CU. A 16-wave grid of few pieces puts
         // four waves on each SIMD of a few CUs and leaves the rest idle, while
         // each wave's decode is one latency-bound chain that runs faster with
-        // fewer waves beside it.
+        // fewer waves beside it. Up to one run per SIMD the kernel of few.hip
+        // decodes it, whose chain is half as long (its 8-byte table and ring
+        // entries leave no room in the LDS for more runs per CU).
         DecodeTuning u = t;
         u.waves = 16;
         DecodeShape s{};
@@ -159,6 +162,16 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
         if (e != hipSuccess) return e;
         const uint64_t pieces = s.units_per_wave ? (s.runs + s.units_per_wave - 1) / s.units_per_wave : 0;
         const uint64_t cus = (uint64_t)device_cus();
+        if (VAR != kAdaptive && s.units_per_wave == 1 && pieces <= kSimdsPerCu * cus) {
+            DecodeParams q = p;
+            q.run = s.units_per_run;
+            q.runs = s.runs;
+            hipError_t fe = hipSuccess;
+            if (decode_few(q, W, sizeof(Sym), shape == nullptr, stream, &fe)) {
+                if (shape) *shape = DecodeShape{s.runs, 1u, s.units_per_run, s.runs, 1u};
+                return fe;
+            }
+        }
         if (pieces <= kSimdsPerCu * cus) u.waves = 1;
         else if (pieces < 16 * cus) u.waves = 8;
         return launch_shape<W, Sym, VAR>(p, u, stream, shape);

@@ -1,0 +1,69 @@
+"""GPU parity of decodes with few runs (one run per workgroup, the bitstream ring holding
+words already looked up). Integer path: exact, into buffers pre-filled with two patterns."""
+
+import numpy as np
+import pytest
+
+from tests.test_gpu_decode import _say, _syms, gpu_decode
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def rc():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2306_12141_amd as m
+    return m
+
+
+def _simds():
+    return 4 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+# Lengths around the super-steps of a run (8 groups; 16 from 256 groups per run on; 4 where
+# 8-group rings do not fit the LDS of a CU's runs), ragged last groups, one run, and as many
+# runs as the chip has SIMDs.
+@pytest.mark.parametrize("W,dt,n,N,M", [
+    (32, np.uint8, 11, 31, 1), (32, np.uint8, 8, 32 * 255 + 5, 1), (32, np.uint8, 12, 32 * 256, 1),
+    (64, np.uint8, 12, 64 * 4 * 256 - 1, 4), (64, np.uint8, 9, 64 * 4 * 256 + 1, 4),
+    (32, np.uint8, 12, 600_011, 3), (64, np.uint16, 12, 600_011, 3), (32, np.uint16, 12, 1_000_003, 700),
+    (64, np.uint16, 13, 400_009, 5), (32, np.uint8, 16, 700_001, 6), (64, np.uint8, 14, 700_001, 900),
+    (64, np.uint8, 12, 2_000_003, 1000), (32, np.uint8, 12, 2_000_003, 1024), (64, np.uint16, 12, 2_000_003, 1024)])
+def test_few_runs(rc, W, dt, n, N, M):
+    _say("case few runs", W, np.dtype(dt).name, n, N, M)
+    A = 256 if dt == np.uint8 else 4096
+    s = _syms(6100 + M, N, A, dt, 1.1)
+    blob = rc.encode(s, lanes=W, quant_bits=n, splits=M, alphabet=A)
+    sh = rc.Plan(blob).shape()
+    assert sh.runs == blob.splits <= _simds()
+    assert (sh.blocks, sh.waves_per_block, sh.units_per_wave) == (sh.runs, 1, 1)
+    assert np.array_equal(gpu_decode(rc, blob), s)
+    for k in (2, 3):
+        assert np.array_equal(gpu_decode(rc, blob, units_per_run=k), s)
+    for P in (1, min(M, 7)):
+        part = rc.encode_partitioned(s, lanes=W, quant_bits=n, partitions=P, alphabet=A)
+        assert np.array_equal(gpu_decode(rc, part), s)
+
+
+@pytest.mark.parametrize("W,dt,n,A", [(32, np.uint8, 12, 256), (64, np.uint8, 16, 256), (32, np.uint16, 12, 4095),
+                                      (64, np.uint16, 16, 4096)])
+@pytest.mark.parametrize("M", [1, 60])
+def test_few_runs_word_rate(rc, W, dt, n, A, M):
+    """Symbols of f = 1 take n bits each (at n = 16 every lane reads a word in every group, the
+    most the ring has to supply) and alternate with stretches of one frequent symbol that
+    hardly reads at all, in blocks of every length against the ring's chunks."""
+    _say("case word rate", W, np.dtype(dt).name, n, A, M)
+    f = np.ones(A, dtype=np.uint32)
+    f[0] = (1 << n) - (A - 1)
+    s = _syms(6300, 40_000 * M + 17, A, dt)
+    at = 0
+    for i, gap in enumerate(_syms(6301, 4 * M, 9_000, np.uint16)):
+        at += 2_000 + 1_000 * i
+        s[at:at + int(gap)] = 0
+        at += int(gap)
+    blob = rc.encode(s, lanes=W, quant_bits=n, splits=M, alphabet=A, freq=f)
+    assert np.array_equal(gpu_decode(rc, blob), s)
+
