@@ -26,9 +26,9 @@ namespace {
 using namespace dev;
 
 template <int W, typename Sym, int K, int SS = 64 / W, int VAR = kPlain>
-__device__ inline void run_item(const DecodeParams &p, uint32_t lut, uint32_t ring0,
+__device__ inline void run_item(const DecodeParams &p, uint32_t ring0,
                                 uint32_t lane, uint32_t wave, uint32_t waves, uint32_t first, uint32_t count) {
-    PairDecoder<W, Sym, K, SS, VAR> d(p, lut, ring0, lane);
+    PairDecoder<W, Sym, K, SS, VAR> d(p, ring0, lane);
     const uint32_t share = wave < count ? (count - 1 - wave) / waves + 1 : 0u;
     uint32_t left = share;
     for (uint32_t q = first + wave; q < first + count; q += waves) d.run(q, --left, share);
@@ -41,8 +41,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(RECOIL_S
     BatchParams bp) {
     using L = Lds<16, K, WAVES>;
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char *lut = smem + L::TABLE;
-    const uint32_t base = lds_addr(smem);   // the first word of the pad holds the popped item
+    unsigned char *lut = smem;
+    const uint32_t base = lds_addr(smem) + bp.lut_bytes;   // the pad, whose first word holds the popped item
     const uint32_t wave = uni(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t ring0 = base + L::PAD + wave * L::WAVE_LDS;
@@ -89,17 +89,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(RECOIL_S
         } else if (d.lanes == 32) {
             if (single) {
                 if (lane < 32) {   // one unit per wave: the upper half-wave idles until the item ends
-                    if (d.symbol_bytes == 1) run_item<32, uint8_t, K, 1, VAR>(p, base + L::TABLE, ring0, lane, wave, WAVES, wi.first, wi.count);
-                    else run_item<32, uint16_t, K, 1, VAR>(p, base + L::TABLE, ring0, lane, wave, WAVES, wi.first, wi.count);
+                    if (d.symbol_bytes == 1) run_item<32, uint8_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
+                    else run_item<32, uint16_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
                 }
             } else if (d.symbol_bytes == 1) {
-                run_item<32, uint8_t, K, 2, VAR>(p, base + L::TABLE, ring0, lane, wave, WAVES, wi.first, wi.count);
+                run_item<32, uint8_t, K, 2, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
             } else {
-                run_item<32, uint16_t, K, 2, VAR>(p, base + L::TABLE, ring0, lane, wave, WAVES, wi.first, wi.count);
+                run_item<32, uint16_t, K, 2, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
             }
         } else {
-            if (d.symbol_bytes == 1) run_item<64, uint8_t, K, 1, VAR>(p, base + L::TABLE, ring0, lane, wave, WAVES, wi.first, wi.count);
-            else run_item<64, uint16_t, K, 1, VAR>(p, base + L::TABLE, ring0, lane, wave, WAVES, wi.first, wi.count);
+            if (d.symbol_bytes == 1) run_item<64, uint8_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
+            else run_item<64, uint16_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
         }
         if (bp.remaining) {
             // Publish the stream's completion once its last item is done: every
@@ -125,7 +125,7 @@ __global__ void reset_head(uint32_t *head) {
 
 template <int K, int WAVES>
 size_t batch_lds(uint32_t lut_bytes) {
-    return Lds<16, K, WAVES>::TABLE + lut_bytes;
+    return Lds<16, K, WAVES>::RINGS + lut_bytes;
 }
 
 template <int K, int WAVES, int VAR = kPlain>

@@ -19,11 +19,10 @@
 //               then one entry per symbol), two LDS reads per symbol.
 // Bitstream ring. Words are fetched in chunks of C = K*W words, the most a unit
 // can consume in K groups (at most one word per symbol, since b >= n). A chunk
-// is requested into registers at the start of a K-group super-step whenever
-// fewer than 2C words remain resident, and written to the ring at its end, so
-// the global-memory latency overlaps K groups of decoding. The ring holds
-// 3C words plus a 64-word mirror of its first 64 slots, so a group's reads
-// never wrap inside a wave.
+// is requested into registers when the one above it is written to the ring, and
+// written when fewer than C words are left, so the global-memory latency overlaps
+// one to three super-steps of K groups and more. The ring holds 3C words plus a
+// mirror of its top C slots, so a super-step's reads never wrap.
 // Synchronisation (Sec. 4.1.1). Lane j is switched on, with its recorded
 // 16-bit state, at the read step of the group its recorded symbol belongs to,
 // just before its first read. Groups above the unit's own range are decoded
@@ -55,27 +54,36 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(RECOIL_S
     using D = PairDecoder<W, Sym, K, SS, VAR>;
     using L = Lds<0, K, WAVES>;
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char *lut = smem + L::TABLE;
-    const uint32_t base = lds_addr(smem);
+    unsigned char *lut = smem;
+    const uint32_t rings = lds_addr(smem) + p.lut_bytes + L::PAD;
+    const uint32_t wave = uni(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t npairs = (p.runs + D::S - 1) / D::S;
+    const uint32_t first = blockIdx.x * WAVES + wave, stride = gridDim.x * WAVES;
+    // Lanes without a coder (W = 32, one unit per wave) mirror the lower half until the
+    // table is staged.
+    D d(p, rings + wave * L::WAVE_LDS, lane & (W * SS - 1u));
+    typename D::First f;
+    bool any = false;
+    if (first < npairs) any = d.request(first, f);
     {
         const uint4 *src = static_cast<const uint4 *>(p.lut);
         const uint32_t chunks = p.lut_bytes / 16;
         for (uint32_t i = threadIdx.x; i < chunks; i += 64 * WAVES) reinterpret_cast<uint4 *>(lut)[i] = src[i];
     }
     __syncthreads();
-    const uint32_t wave = uni(threadIdx.x >> 6);
-    const uint32_t lane = threadIdx.x & 63u;
-    if (W * SS < 64 && lane >= (uint32_t)(W * SS)) return;   // lanes without a coder (no barrier follows)
-    const uint32_t npairs = (p.runs + D::S - 1) / D::S;
-    const uint32_t first = blockIdx.x * WAVES + wave, stride = gridDim.x * WAVES;
-    D d(p, base + L::TABLE, base + L::PAD + wave * L::WAVE_LDS, lane);
+    if (W * SS < 64 && lane >= (uint32_t)(W * SS)) return;   // no barrier follows
     // Pairs are dealt out by position. The issue arbiter favours older waves,
     // which would leave the youngest waves holding the last pairs of the launch
     // alone (a shared work counter costs more: same-address atomics serialise).
     // Instead each wave's priority follows the part of its share still left.
     const uint32_t share = first < npairs ? (npairs - 1 - first) / stride + 1 : 0u;
     uint32_t left = share;
-    for (uint32_t pair = first; pair < npairs; pair += stride) d.run(pair, --left, share);
+    for (uint32_t pair = first; pair < npairs; any = pair < npairs && d.request(pair, f)) {
+        --left;
+        if (any) d.run(f, left, share);
+        pair += stride;
+    }
 }
 
 template <typename Sym>
@@ -85,7 +93,7 @@ __global__ __launch_bounds__(256) void fill_symbol(Sym *out, uint64_t n, Sym v) 
 
 template <int K, int WAVES>
 size_t lds_bytes(uint32_t lut_bytes) {
-    return Lds<0, K, WAVES>::TABLE + (size_t)lut_bytes;
+    return Lds<0, K, WAVES>::RINGS + (size_t)lut_bytes;
 }
 
 template <int W, typename Sym, int K, int WAVES, int SS, int VAR>

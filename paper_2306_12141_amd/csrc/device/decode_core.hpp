@@ -11,16 +11,16 @@
 //
 // Bitstream ring (per unit, in LDS). Words are fetched from HBM in chunks of
 // C = K*W words, the most a unit can consume in a super-step of K groups (one
-// word per symbol at most, since b >= n). A chunk is requested into registers
-// at the start of a super-step whenever fewer than 2C words stay resident and is
-// written to the ring at its end. The ring has 3C slots plus a C-word mirror of
+// word per symbol at most, since b >= n). A chunk is requested into registers when
+// the one above it is written to the ring, and written when fewer than C words are
+// left. The ring has 3C slots plus a C-word mirror of
 // its top chunk placed below slot 0, so reads never wrap inside a super-step:
 // word w lives at slot w mod 3C, and positions down to -C read the mirror.
 //
 // Per group the scalar unit only advances the LDS address of the unit's next
 // word by twice the number of reading lanes (one s_bcnt1 and one s_lshl1_add
 // per unit); the per-group store offsets are immediates of the unrolled
-// super-step. The ring read is unconditional and selected with v_cndmask.
+// super-step.
 //
 // Synchronisation (Sec. 4.1.1): lane j is switched on with its recorded 16-bit
 // state at the read step of the group its recorded symbol belongs to, just
@@ -66,15 +66,15 @@ struct Table;
 template <>
 struct Table<uint8_t> {
     using Entry = uint32_t;   // symbol | f << 8 | (slot - F) << 20
-    __device__ static inline uint32_t step(uint32_t lut, uint32_t &x, uint32_t n, uint32_t mask) {
-        const Entry e = lds_ld<Entry>(lut + ((x & mask) << 2));
+    __device__ static inline uint32_t step(uint32_t &x, uint32_t n, uint32_t mask) {
+        const Entry e = lds_ld<Entry>((x & mask) << 2);
         const uint32_t f = (e >> 8) & 0xFFFu;
         x = __umul24(f, x >> n) + (e >> 20);
         return e;             // the low byte is the symbol
     }
     // Adaptive coding: the symbol's own table t of the 2^n-entry tables laid end to end.
-    __device__ static inline uint32_t step_t(uint32_t lut, uint32_t &x, uint32_t n, uint32_t mask, uint32_t t) {
-        const Entry e = lds_ld<Entry>(lut + (((t << n) | (x & mask)) << 2));
+    __device__ static inline uint32_t step_t(uint32_t &x, uint32_t n, uint32_t mask, uint32_t t) {
+        const Entry e = lds_ld<Entry>(((t << n) | (x & mask)) << 2);
         const uint32_t f = (e >> 8) & 0xFFFu;
         x = __umul24(f, x >> n) + (e >> 20);
         return e;
@@ -84,8 +84,8 @@ struct Table<uint8_t> {
 template <>
 struct Table<uint16_t> {
     using Entry = u32x2;      // .x = f | (slot - F) << 16, .y = symbol
-    __device__ static inline uint32_t step(uint32_t lut, uint32_t &x, uint32_t n, uint32_t mask) {
-        const Entry e = lds_ld<Entry>(lut + ((x & mask) << 3));
+    __device__ static inline uint32_t step(uint32_t &x, uint32_t n, uint32_t mask) {
+        const Entry e = lds_ld<Entry>((x & mask) << 3);
         x = __umul24(e.x & 0xFFFFu, x >> n) + (e.x >> 16);
         return e.y;
     }
@@ -97,11 +97,11 @@ struct Table<uint16_t> {
 template <typename Sym>
 struct WideTable {
     using Entry = u32x2;
-    __device__ static inline uint32_t step(uint32_t lut, uint32_t &x, uint32_t n, uint32_t mask) {
+    __device__ static inline uint32_t step(uint32_t &x, uint32_t n, uint32_t mask) {
         const uint32_t slot = x & mask;
-        const uint32_t c = lds_ld<uint32_t>(lut + ((slot >> 4) << 2));
+        const uint32_t c = lds_ld<uint32_t>((slot >> 4) << 2);
         const uint32_t r = (c >> 16) + __builtin_popcount(__builtin_amdgcn_ubfe(c, 0, slot & 15u));
-        const Entry e = lds_ld<Entry>(lut + ((mask + 1u) >> 2) + (r << 3));
+        const Entry e = lds_ld<Entry>(((mask + 1u) >> 2) + (r << 3));
         x = __umul24(e.x, x >> n) + slot - (e.y >> 16);
         return e.y;
     }
@@ -119,14 +119,16 @@ struct Geo {
     static_assert(sizeof(Chunk) == LANE_BYTES, "chunk slice must be 8 or 16 bytes");
 };
 
-// LDS layout of a workgroup: [pad][rings of every wave][decode table]. The
-// pad is a 16-byte slot the batched kernel uses to broadcast its work item.
+// LDS layout of a workgroup: [decode table][pad][rings of every wave]. The table is at
+// LDS address 0 (the kernels have no other shared memory), so that an entry's address is
+// its slot shifted. The pad is a 16-byte slot the batched kernel uses to broadcast its
+// work item.
 template <int PADB, int K, int WAVES>
 struct Lds {
     static constexpr uint32_t PAD = PADB;
     static constexpr uint32_t WAVE_LDS = Geo<32, K>::WAVE_LDS > Geo<64, K>::WAVE_LDS ? Geo<32, K>::WAVE_LDS
                                                                                      : Geo<64, K>::WAVE_LDS;
-    static constexpr uint32_t TABLE = PAD + WAVES * WAVE_LDS;
+    static constexpr uint32_t RINGS = PAD + WAVES * WAVE_LDS;   // bytes after the table
 };
 
 __device__ inline uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -168,6 +170,55 @@ __device__ inline T uni_load(const T *src) {
 // fit are kept in VGPR lanes and mostly reloaded outside the group loops).
 #define RECOIL_SGPR_BUDGET 64
 
+// The read step after the compare has left the reading lanes in VCC (two wait states
+// before a vector instruction reads VCC as a scalar operand: the move and the count).
+#define RECOIL_READ_TAIL                 \
+    "s_and_saveexec_b64 %[sv], vcc\n\t"  \
+    "ds_read_u16 %[w], %[t]\n\t"         \
+    "v_lshlrev_b32 %[x], 16, %[x]\n\t"   \
+    "s_mov_b64 exec, %[sv]\n\t"
+#define RECOIL_READ_64                             \
+    "v_mov_b32 %[w], 0\n\t"                        \
+    "s_bcnt1_i32_b64 %[c], vcc\n\t"                \
+    "v_mbcnt_lo_u32_b32 %[t], vcc_lo, 0\n\t"       \
+    "v_mbcnt_hi_u32_b32 %[t], vcc_hi, %[t]\n\t"    \
+    "v_lshl_add_u32 %[t], %[t], 1, %[a]\n\t"       \
+    RECOIL_READ_TAIL                               \
+    "s_lshl1_add_u32 %[a], %[c], %[a]\n\t"         \
+    "s_waitcnt lgkmcnt(0)\n\t"                     \
+    "v_or_b32 %[x], %[x], %[w]"
+#define RECOIL_READ_32                             \
+    "v_mov_b32 %[w], 0\n\t"                        \
+    "s_bcnt1_i32_b32 %[c], vcc_lo\n\t"             \
+    "v_mbcnt_lo_u32_b32 %[t], vcc_lo, 0\n\t"       \
+    "v_lshl_add_u32 %[t], %[t], 1, %[a]\n\t"       \
+    RECOIL_READ_TAIL                               \
+    "s_lshl1_add_u32 %[a], %[c], %[a]\n\t"         \
+    "s_waitcnt lgkmcnt(0)\n\t"                     \
+    "v_or_b32 %[x], %[x], %[w]"
+// Pairs: readers below the lane in its own half-wave (the lower half's are masked off for
+// upper lanes), counted onto the unit's address; each unit's address then advances by its
+// own readers, e += pl + upper * (ph - pl) (a vector instruction reads at most one scalar
+// operand, so the two counts cannot be selected per lane in one).
+#define RECOIL_READ_PAIR                           \
+    "v_mov_b32 %[w], 0\n\t"                        \
+    "s_bcnt1_i32_b32 %[c], vcc_lo\n\t"             \
+    "v_and_b32 %[t], vcc_lo, %[low]\n\t"           \
+    "s_bcnt1_i32_b32 %[d], vcc_hi\n\t"             \
+    "v_mbcnt_lo_u32_b32 %[t], %[t], %[e]\n\t"      \
+    "v_mbcnt_hi_u32_b32 %[t], vcc_hi, %[t]\n\t"    \
+    "s_sub_i32 %[d], %[d], %[c]\n\t"               \
+    "v_lshlrev_b32 %[t], 1, %[t]\n\t"              \
+    RECOIL_READ_TAIL                               \
+    "v_mad_i32_i24 %[e], %[up], %[d], %[e]\n\t"    \
+    "v_add_u32 %[e], %[c], %[e]\n\t"               \
+    "s_waitcnt lgkmcnt(0)\n\t"                     \
+    "v_or_b32 %[x], %[x], %[w]"
+
+struct ScalarLim {
+    uint32_t v;
+};
+
 // Kernel variants: kCount also adds 1 to counts[i] for every store of symbol i (a
 // checking launch); kAdaptive codes symbol i with decode table tidx[i] (adaptive
 // coding, uint8 symbols); kWide reads the two-level table of 13 <= n <= 16.
@@ -189,10 +240,11 @@ struct PairDecoder {
     static_assert(!ADAPT || sizeof(Sym) == 1, "adaptive decoding reads the table index at the symbol's byte offset");
 
     const DecodeParams &p;
-    uint32_t lut;          // LDS address of the decode table
     uint32_t ring0;        // LDS address of this wave's first unit
     uint32_t lane, col, upper, coder;
     uint32_t lane_ring;    // this lane's chunk-slice address in the top third of its unit's ring
+    // In vector registers, all lanes alike: an and or a shift of vector registers only
+    // issues every two cycles, one with a scalar operand every four.
     uint32_t n, mask;
 
     // Per unit of the pair (wave-uniform). Kept few: the register file holds
@@ -209,7 +261,7 @@ struct PairDecoder {
     int32_t vres;          // words of the unit still in the ring: (next word + 1) - vfq * C
     int32_t vfq;           // lowest chunk held in the ring (the next fetch is vfq - 1)
     uint32_t vpo;          // byte offset from the top third of the third that chunk vfq - 1 goes to
-    // Pairs (S == 2): the LDS byte address of the next word of the lane's unit, the
+    // Pairs (S == 2): the LDS address (in words) of the next word of the lane's unit, the
     // address at which it wraps, and a mask that confines a read ballot to the
     // lane's own half-wave.
     uint32_t vb, vlim, lowmask;
@@ -224,13 +276,14 @@ struct PairDecoder {
     uint32_t quad_off;     // QUAD: this lane's dword offset from the fast body's group pointer, plus 3W
     bool active;
 
-    __device__ PairDecoder(const DecodeParams &p_, uint32_t lut_, uint32_t ring0_, uint32_t lane_)
-        : p(p_), lut(lut_), ring0(ring0_), lane(lane_) {
+    __device__ PairDecoder(const DecodeParams &p_, uint32_t ring0_, uint32_t lane_)
+        : p(p_), ring0(ring0_), lane(lane_) {
         col = lane & (W - 1);
         upper = (S == 2) ? (lane >> 5) : 0u;
         coder = W - 1 - col;
         n = p.quant_bits;
         mask = (1u << n) - 1u;
+        asm volatile("" : "+v"(n), "+v"(mask));
         lane_ring = lane_ring_addr();
     }
 
@@ -244,10 +297,10 @@ struct PairDecoder {
     // Byte offset, from the top third, of the third holding chunk q.
     __device__ static inline uint32_t third_off(int32_t q) { return 2u * C * (uint32_t)(2 - q % 3); }
 
-    // This lane's slice of chunk q (uniform q): a scalar base plus a fixed lane offset.
+    // This lane's slice of chunk q, by a 32-bit byte offset from the scalar bitstream base.
     __device__ inline Chunk fetch(int32_t q) const {
-        const unsigned char *base = reinterpret_cast<const unsigned char *>(p.words) + (uint64_t)(uint32_t)q * (2 * C);
-        return *reinterpret_cast<const Chunk *>(base + col * (uint32_t)sizeof(Chunk));
+        const uint32_t off = (uint32_t)q * (2 * C) + col * (uint32_t)sizeof(Chunk);
+        return *reinterpret_cast<const Chunk *>(reinterpret_cast<const unsigned char *>(p.words) + off);
     }
 
     // This lane's slice (K words, ascending) of a chunk into the ring third at
@@ -275,121 +328,134 @@ struct PairDecoder {
     // highest unit's split point (records, first word, first group, completion
     // point) and ends at its lowest unit's last group; the split points in
     // between are not used (Sec. 3.3).
-    __device__ bool begin(uint32_t pair) {
-        const uint32_t r0 = pair * S;
-        bool any = false;
-        bool has_last = false;
-        uint32_t sync_max = 0;
-        int32_t cur[S];
-        uint32_t top[S], ghi[S];
-#pragma unroll
-        for (uint32_t h = 0; h < S; ++h) {
-            const uint32_t r = r0 + h;
-            const bool valid = r < p.runs;
-            const uint32_t lo = r * p.run;
-            const uint32_t hi = valid ? min(lo + p.run, p.units) - 1u : 0u;
-            const bool last = valid && hi + 1 == p.units;
-            const bool full = last || (valid && p.partitioned);   // starts from 32-bit final states
-            UnitMeta m = {0, 0, 0, 1};
-            if (valid) {
-                m = p.meta[hi];
-                m.glo = p.meta[lo].glo;
-            }
-            cur[h] = (int32_t)uni(m.next);
-            top[h] = uni(m.top);
-            ghi[h] = uni(m.ghi);
-            const uint32_t glo = uni(m.glo);
-            steps[h] = (valid && top[h] + 1 > glo) ? top[h] + 1 - glo : 0u;
-            uint32_t sync = valid ? top[h] - ghi[h] + 1 : 0u;
-            if (full) sync = (last && (p.n_symbols % W)) ? 1u : 0u;   // only the stream's last group is ragged
-            has_last = has_last || full;
-            sync_max = max(sync_max, sync);
-            any = any || steps[h] > 0;
+    //
+    // request() reads the records and requests the first chunks, fill() writes them to
+    // the ring: two rounds of memory latency, with the loads of both units of a pair and
+    // of all chunks in flight together. request() touches no LDS, so the decode table is
+    // staged under the second. Two chunks: the least that leaves C words resident whatever
+    // the first word's place in its chunk (every wave of the launch asks for them at once,
+    // and a third one delays the first group by its share of the bandwidth).
+    // Before (a chunk at a time, the units of a pair one after the other, the table
+    // first) a 64 MiB stream at W = 32 in 16384 units took 43.1 us, now 41.0.
+    static constexpr int32_t kFill = 2;
+    struct First {
+        Chunk c[kFill];
+        int32_t q0;            // the lane's unit's highest chunk (-1: none)
+    };
+    __device__ inline bool request(uint32_t pair, First &f) {
+        const uint32_t mine = pair * S + upper;
+        const bool valid = mine < p.runs;
+        const uint32_t lo = valid ? mine * p.run : 0u, hi = valid ? min(lo + p.run, p.units) - 1u : 0u;
+        const bool last = valid && hi + 1 == p.units;
+        const bool full = last || (valid && p.partitioned);   // starts from 32-bit final states
+        UnitMeta m = p.meta[hi];
+        m.glo = p.meta[lo].glo;
+        rec = p.lanes[(uint64_t)hi * W + coder];
+        if (!valid) {
+            m = UnitMeta{0, 0, 0, 1};
+            rec = 0u;
         }
-        presync = sync_max;
-        sync_lean = !has_last;
-        top0 = top[0];
-        top_min = S == 2 ? min(top[0], top[S - 1]) : top[0];
-        my_top = S == 2 && upper ? top[S - 1] : top[0];
-        my_ghi = S == 2 && upper ? ghi[S - 1] : ghi[0];
-        my_steps = S == 2 && upper ? steps[S - 1] : steps[0];
+        my_top = m.top;
+        my_ghi = m.ghi;
+        my_steps = valid && m.top + 1 > m.glo ? m.top + 1 - m.glo : 0u;
+        uint32_t sync = valid ? m.top - m.ghi + 1 : 0u;
+        if (full) sync = (last && (p.n_symbols % W)) ? 1u : 0u;   // only the stream's last group is ragged
+        x = full ? rec : 0u;
+        active = full;
+        act = full ? 0u : (rec >> 16);
+        sync_lean = __ballot(full) == 0;
+        top0 = uni(my_top);
+        steps[0] = uni(my_steps);
+        presync = uni(sync);
+        top_min = top0;
+        if constexpr (S == 2) {
+            const uint32_t t1 = __builtin_amdgcn_readlane(my_top, 32), s1 = __builtin_amdgcn_readlane(sync, 32);
+            steps[1] = __builtin_amdgcn_readlane(my_steps, 32);
+            top_min = min(top0, t1);
+            presync = max(presync, s1);
+        }
         // Fast-body store offset of this lane from unit 0's group pointer.
         lane_off = (coder + (S == 2 ? upper * W * (my_top - top0) : 0u)) * (uint32_t)sizeof(Sym);
         // Lane 4a + b of a quad writes group b of a block of four, at the column of
         // the quad's highest lane (its lowest coder): 3 - b columns below its own.
         quad_off = lane_off - 3u + (lane & 3u) + (3u - (lane & 3u)) * W;
-        const uint32_t mine = r0 + upper;
-        const bool my_valid = mine < p.runs;
-        const uint32_t my_hi = my_valid ? min(mine * p.run + p.run, p.units) - 1u : 0u;
-        const bool my_full = my_valid && (my_hi + 1 == p.units || p.partitioned);
-        rec = my_valid ? p.lanes[(uint64_t)my_hi * W + coder] : 0u;
-        x = my_full ? rec : 0u;
-        active = my_full;
-        act = my_full ? 0u : (rec >> 16);
-        // Initial fill: the chunk holding word cur-1 and the two below it.
-        int32_t q0[S], fq[S], res[S];
-        uint32_t po[S];
-#pragma unroll
-        for (uint32_t h = 0; h < S; ++h) {
-            q0[h] = cur[h] > 0 ? (cur[h] - 1) / (int32_t)C : -1;
-            fq[h] = q0[h] >= 2 ? q0[h] - 2 : 0;
-            res[h] = cur[h] - fq[h] * (int32_t)C;
-            ua[h] = uni(ring_addr(h, cur[h] > 0 ? (cur[h] - 1) % (int32_t)R : 0));
-            po[h] = third_off(fq[h] + 2);      // chunk fq - 1 shares a third with fq + 2
-        }
-        const bool hi = S == 2 && upper;
-        vfq = hi ? fq[S - 1] : fq[0];
-        vres = hi ? res[S - 1] : res[0];
-        vpo = hi ? po[S - 1] : po[0];
+        const int32_t cur = (int32_t)m.next;
+        f.q0 = cur > 0 ? (cur - 1) / (int32_t)C : -1;
+        vfq = max(f.q0 - (kFill - 1), 0);
+        vres = cur - vfq * (int32_t)C;
+        vpo = third_off(vfq + 2);      // chunk vfq - 1 shares a third with vfq + 2
+        const uint32_t at = ring_addr(upper, cur > 0 ? (cur - 1) % (int32_t)R : 0);
         if constexpr (S == 2) {
-            vb = hi ? ua[S - 1] : ua[0];
-            vlim = ring_addr(upper, -1);
+            vb = at >> 1;
+            vlim = ring_addr(upper, -1) >> 1;
             lowmask = upper ? 0u : 0xFFFFFFFFu;
+        } else {
+            ua[0] = uni(at);
+            vfq = (int32_t)uni((uint32_t)vfq);
+            vres = (int32_t)uni((uint32_t)vres);
+            vpo = uni(vpo);
         }
 #pragma unroll
-        for (uint32_t h = 0; h < S; ++h)
-            for (int32_t q = q0[h]; q >= 0 && q > q0[h] - 3; --q)
-                if (S == 1 || upper == h) put_chunk(third_off(q), fetch(q));
-        return any;
+        for (int32_t i = 0; i < kFill; ++i) f.c[i] = fetch(max(f.q0 - i, 0));
+        return steps[0] > 0 || (S == 2 && steps[S - 1] > 0);
+    }
+    __device__ inline void fill(First &f) {
+#pragma unroll
+        for (int32_t i = 0; i < kFill; ++i) {
+            // Both loads are waited for here, also where a chunk is not used: a load that
+            // may still be in flight in the loops costs them a wait for every store.
+            asm volatile("" : "+v"(f.c[i]));
+            if (f.q0 >= i) put_chunk(third_off(f.q0 - i), f.c[i]);
+        }
     }
 
-    // One group's read step. need is this lane's "x < L" (and live). For one unit
-    // per wave, a is the unit's scalar LDS address of its next word; for a pair, e
-    // is the lane's own unit's address (a vector register), so that the address
-    // chain of a group (ballot, count, address, LDS read) has no scalar step.
-    template <uint32_t G_IDX>
-    __device__ inline void read_step(bool need, uint32_t &a, uint32_t &e) {
-        const uint64_t bal = __ballot(need);
-        const uint32_t bl = (uint32_t)bal, bh = (uint32_t)(bal >> 32);
-        uint32_t addr;
-        if constexpr (S == 1) {
-            const uint32_t m = __builtin_amdgcn_mbcnt_hi(bh, __builtin_amdgcn_mbcnt_lo(bl, 0u));
-            // The lane's word is m words above the unit's top word (descending ring);
-            // a stays an opaque SGPR byte address so the address is one v_lshl_add.
-            asm volatile("" : "+s"(a));
-            addr = (m << 1) + a;
-            a = s_lshl1_add((uint32_t)__builtin_popcountll(bal), a);
+    // One group's read step: the lanes with x < lim take a word each. For one unit per wave,
+    // a is the unit's scalar LDS address of its next word; for a pair, e is the address of
+    // the lane's own unit in words (a vector register), so that the address chain of a group
+    // (compare, count, address, LDS read) has no scalar step.
+    //
+    // Written out because the issue of vector instructions bounds the decode (a wave64 add,
+    // and, or, shift or move of vector registers takes two cycles of its SIMD, every other
+    // instruction used here four): a lane that reads nothing adds a zero word to its
+    // unshifted state, so the renormalisation is a masked shift and an or instead of a
+    // shift-or and a select; what the address and the read do not wait for stands under
+    // their latency. The wait for the read is in here with it. Against the compiler's form
+    // (unmasked read, shift-or, select, scalar operands): 64 MiB at W = 32 in 16384 units
+    // 44.3 -> 43.1 us, at n = 16 57.5 -> 52.1; 256 MiB at W = 32 144 -> 141; at W = 64
+    // 117.4 -> 116.5, within the runs' spread.
+    template <typename Lim>
+    __device__ inline void read_step(Lim lim_, uint32_t &a, uint32_t &e) {
+        uint32_t w, t, c, d;
+        uint64_t sv;
+        if constexpr (S == 2) {
+            if constexpr (std::is_same<Lim, ScalarLim>::value)
+                asm volatile("v_cmp_gt_u32 vcc, %[lim], %[x]\n\t" RECOIL_READ_PAIR
+                             : [x] "+v"(x), [e] "+v"(e), [w] "=&v"(w), [t] "=&v"(t), [c] "=&s"(c), [d] "=&s"(d), [sv] "=&s"(sv)
+                             : [lim] "s"(lim_.v), [low] "v"(lowmask), [up] "v"(upper) : "vcc", "scc");
+            else
+                asm volatile("v_cmp_gt_u32 vcc, %[lim], %[x]\n\t" RECOIL_READ_PAIR
+                             : [x] "+v"(x), [e] "+v"(e), [w] "=&v"(w), [t] "=&v"(t), [c] "=&s"(c), [d] "=&s"(d), [sv] "=&s"(sv)
+                             : [lim] "v"(lim_), [low] "v"(lowmask), [up] "v"(upper) : "vcc", "scc");
+        } else if constexpr (W == 64) {
+            if constexpr (std::is_same<Lim, ScalarLim>::value)
+                asm volatile("v_cmp_gt_u32 vcc, %[lim], %[x]\n\t" RECOIL_READ_64
+                             : [x] "+v"(x), [a] "+s"(a), [w] "=&v"(w), [t] "=&v"(t), [c] "=&s"(c), [sv] "=&s"(sv)
+                             : [lim] "s"(lim_.v) : "vcc", "scc");
+            else
+                asm volatile("v_cmp_gt_u32 vcc, %[lim], %[x]\n\t" RECOIL_READ_64
+                             : [x] "+v"(x), [a] "+s"(a), [w] "=&v"(w), [t] "=&v"(t), [c] "=&s"(c), [sv] "=&s"(sv)
+                             : [lim] "v"(lim_) : "vcc", "scc");
         } else {
-            // Readers below the lane in its own half-wave: the lower half's ballot is
-            // masked off for upper lanes before the count (one v_and with the scalar
-            // ballot; the opaque mask keeps the compiler from turning it into selects).
-            asm volatile("" : "+v"(lowmask));
-            const uint32_t m = __builtin_amdgcn_mbcnt_hi(bh, __builtin_amdgcn_mbcnt_lo(bl & lowmask, 0u));
-            addr = (m << 1) + e;
-            // Each unit's address advances by twice its own readers, off the address
-            // chain of this group: e += 2 pl + upper * 2 (ph - pl). (A VALU instruction
-            // reads at most one scalar operand, so the two counts cannot be selected
-            // per lane in one instruction.)
-            const int32_t pl = __builtin_popcount(bl), ph = __builtin_popcount(bh);
-            const int32_t dd = 2 * (ph - pl);
-            uint32_t t;
-            asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(t) : "v"(upper), "s"(dd), "v"(e));
-            asm("v_lshl_add_u32 %0, %1, 1, %2" : "=v"(e) : "s"(pl), "v"(t));
+            if constexpr (std::is_same<Lim, ScalarLim>::value)
+                asm volatile("v_cmp_gt_u32 vcc, %[lim], %[x]\n\t" RECOIL_READ_32
+                             : [x] "+v"(x), [a] "+s"(a), [w] "=&v"(w), [t] "=&v"(t), [c] "=&s"(c), [sv] "=&s"(sv)
+                             : [lim] "s"(lim_.v) : "vcc", "scc");
+            else
+                asm volatile("v_cmp_gt_u32 vcc, %[lim], %[x]\n\t" RECOIL_READ_32
+                             : [x] "+v"(x), [a] "+s"(a), [w] "=&v"(w), [t] "=&v"(t), [c] "=&s"(c), [sv] "=&s"(sv)
+                             : [lim] "v"(lim_) : "vcc", "scc");
         }
-        uint32_t w = lds_ld<uint16_t>(addr);
-        // Keep the read unconditional: lanes that do not need it read an in-ring word and drop it.
-        asm volatile("" : "+v"(w));
-        x = need ? ((x << 16) | w) : x;
+        if constexpr (S == 1) a = uni(a);   // no instruction: tells the compiler that the sum is uniform
     }
 
     // This lane's table indices of the K groups from group top0 - k down (the bytes
@@ -441,10 +507,10 @@ struct PairDecoder {
 
     template <uint32_t G_IDX>
     __device__ inline void group_fast(uint32_t &a, uint32_t &e, unsigned char *outh, uint32_t (&held)[4]) {
-        read_step<G_IDX>(x < kL, a, e);
+        read_step(ScalarLim{kL}, a, e);
         uint32_t s;
-        if constexpr (ADAPT) s = T::step_t(lut, x, n, mask, tcur[G_IDX]);
-        else s = T::step(lut, x, n, mask);
+        if constexpr (ADAPT) s = T::step_t(x, n, mask, tcur[G_IDX]);
+        else s = T::step(x, n, mask);
         if constexpr (QUAD) {
             held[G_IDX & 3u] = s;
             if constexpr ((G_IDX & 3u) == 3u) store_quad<G_IDX - 3u>(outh, held);
@@ -464,13 +530,13 @@ struct PairDecoder {
             active = true;
             x = rec & 0xFFFFu;
         }
-        read_step<G_IDX>(live && active && x < kL, a, e);
+        read_step(live && active ? kL : 0u, a, e);
         const uint32_t h = my_top - k;
         const uint64_t i = (uint64_t)h * W + coder;
         if (live && active && i < p.n_symbols) {
             uint32_t s;
-            if constexpr (ADAPT) s = T::step_t(lut, x, n, mask, tcur[G_IDX]);
-            else s = T::step(lut, x, n, mask);
+            if constexpr (ADAPT) s = T::step_t(x, n, mask, tcur[G_IDX]);
+            else s = T::step(x, n, mask);
             if (h <= my_ghi) {
                 static_cast<Sym *>(p.out)[i] = (Sym)s;
                 if constexpr (COUNT) count_store(i);
@@ -489,13 +555,11 @@ struct PairDecoder {
         const bool on = k == act;
         x = on ? (rec & 0xFFFFu) : x;
         lim = on ? kL : lim;
-        read_step<G_IDX>(x < lim, a, e);
-        uint32_t lb = lut;
-        asm volatile("" : "+s"(lb));   // the table base as a scalar operand of the address
+        read_step(lim, a, e);
         const uint32_t h = my_top - k;
         uint32_t s;
-        if constexpr (ADAPT) s = T::step_t(lb, x, n, mask, tcur[G_IDX]);
-        else s = T::step(lb, x, n, mask);
+        if constexpr (ADAPT) s = T::step_t(x, n, mask, tcur[G_IDX]);
+        else s = T::step(x, n, mask);
         if (h <= my_ghi) {
             static_cast<Sym *>(p.out)[(uint64_t)h * W + coder] = (Sym)s;
             if constexpr (COUNT) count_store((uint64_t)h * W + coder);
@@ -521,15 +585,20 @@ struct PairDecoder {
         }
     }
 
-    // K groups. At the start, every unit with fewer than 2C words resident
-    // requests its next chunk into registers; the chunk is written to the ring
-    // after the K groups, so the load overlaps them. (Every step consumes at
-    // most C words, so a unit keeps at least C words resident, and reads stay
-    // within the ring plus its mirror.) Returns false if a unit read past its
-    // first word (corrupt split data).
+    // K groups. Every step consumes at most C words and starts with at least C resident, so
+    // reads stay within the ring plus its mirror.
+    // Fast super-steps: the units left with fewer than C words write the chunk they
+    // requested when they wrote the one above it (pre) to the ring, and request the next.
+    // A request is then in flight for as long as a chunk lasts, one to three super-steps and
+    // more; one super-step does not cover the latency of a cold read (before, adaptive
+    // decoding of 32 Mi symbols took 53.5 us in pairs, now 47.0; n = 16, 64 MiB, 48.2 and
+    // 46.8). At most 2C words are left when a chunk is written, so its third is free.
+    // The others: every unit with fewer than 2C words requests its next chunk at the start
+    // and writes it at the end.
+    // Returns false if a unit read past its first word (corrupt split data).
     // fend: fast super-steps of the current loop are those at k' with k' + K <= fend.
     template <int MODE, uint32_t KK = K>
-    __device__ inline bool super_step(uint32_t k, uint32_t fend = 0) {
+    __device__ inline bool super_step(uint32_t k, Chunk &pre, uint32_t fend = 0) {
         if constexpr (ADAPT && MODE == kFast) {
             // Table indices: this super-step's unless fetched ahead, and the next
             // one's when it is also fast (its groups are then inside the stream).
@@ -538,38 +607,35 @@ struct PairDecoder {
         } else if constexpr (ADAPT) {
             load_tidx_checked<KK>(k);
         }
-        // Per lane: does this lane's unit fetch? (Uniform within each half-wave.)
-        const bool need = (MODE != kPred || my_steps > k) && vfq > 0 && vres < 2 * (int32_t)C;
         uint32_t a = ua[0], e = S == 2 ? vb : 0u;
-        if (__ballot(need)) {
-            // One load for the whole wave, each unit's lanes addressing their own
-            // chunk by a 32-bit byte offset from the scalar bitstream base (lanes of
-            // a unit that does not fetch load an in-range chunk and drop it). The
-            // registers stay untouched until the K groups are done; the empty asm
-            // keeps the scheduler from hoisting the chunk's use (and its wait on
-            // the load) into the groups.
-            const uint32_t off = (uint32_t)max(vfq - 1, 0) * (2 * C);
-            Chunk pre = *reinterpret_cast<const Chunk *>(reinterpret_cast<const unsigned char *>(p.words) +
-                                                         (off + col * (uint32_t)sizeof(Chunk)));
-            groups<MODE>(std::make_integer_sequence<uint32_t, KK>{}, k, a, e);
-            asm volatile("" : "+v"(pre));
-            if (need) {
-                put_chunk(vpo, pre);
-                vfq -= 1;
-                vres += (int32_t)C;
-                vpo = vpo == 4 * C ? 0u : vpo + 2 * C;
-            }
-        } else {
-            groups<MODE>(std::make_integer_sequence<uint32_t, KK>{}, k, a, e);
+        bool need = false;
+        if constexpr (MODE != kFast) {
+            // (Lanes of a unit that does not fetch load an in-range chunk and drop it; the
+            // empty asm below keeps the chunk's use, and its wait, out of the groups.)
+            need = (MODE != kPred || my_steps > k) && vfq > 0 && vres < 2 * (int32_t)C;
+            pre = fetch(max(vfq - 1, 0));
         }
+        groups<MODE>(std::make_integer_sequence<uint32_t, KK>{}, k, a, e);
         // Words the lane's unit consumed, from its address advance; an address that
         // moved into the mirror (below slot 0) wraps to the ring's top.
         if constexpr (S == 1) {
             vres -= (int32_t)((a - ua[0]) >> 1);
             ua[0] = a >= ring_addr(0, -1) ? a - 2 * R : a;
         } else {
-            vres -= (int32_t)((e - vb) >> 1);
-            vb = e >= vlim ? e - 2 * R : e;
+            vres -= (int32_t)(e - vb);
+            vb = e >= vlim ? e - R : e;
+        }
+        // Per lane: does this lane's unit put a chunk? (Uniform within each half-wave.)
+        if constexpr (MODE == kFast) need = vfq > 0 && vres < (int32_t)C;
+        else asm volatile("" : "+v"(pre));
+        if (S == 1 ? need : __ballot(need) != 0) {
+            if (need) {
+                put_chunk(vpo, pre);
+                vfq -= 1;
+                vres += (int32_t)C;
+                vpo = vpo == 4 * C ? 0u : vpo + 2 * C;
+                if constexpr (MODE == kFast) pre = fetch(max(vfq - 1, 0));
+            }
         }
         if constexpr (ADAPT && MODE == kFast) {
 #pragma unroll
@@ -587,7 +653,11 @@ struct PairDecoder {
     // given precedence so that all end together, and the last level, in which
     // the oldest wave goes first again, is kept short.
     __device__ void run(uint32_t pair, uint32_t left, uint32_t share) {
-        if (!begin(pair)) return;
+        First f;
+        if (request(pair, f)) run(f, left, share);
+    }
+    __device__ void run(First &f, uint32_t left, uint32_t share) {
+        fill(f);
         uint32_t kmax = 0, kmin = 0xFFFFFFFFu;
 #pragma unroll
         for (uint32_t h = 0; h < S; ++h) {
@@ -605,16 +675,17 @@ struct PairDecoder {
         // of the pair does.
         bool ok = true;
         uint32_t k = 0;
+        Chunk pre;
         // The lean body needs every unit within its own groups for the whole
         // lead-in; it does not track which lanes are on, so afterwards (when all
         // are) the flag is set for the predicated body of the end.
         const uint32_t lead = (presync + K / 2 - 1) / (K / 2) * (K / 2);
         if (sync_lean && lead <= kmin) {
             lim = 0;
-            for (; ok && k < presync; k += K / 2) ok = super_step<kSync, K / 2>(k);
+            for (; ok && k < presync; k += K / 2) ok = super_step<kSync, K / 2>(k, pre);
             active = true;
         } else {
-            for (; ok && k < kmax && k < presync; k += K / 2) ok = super_step<kPred, K / 2>(k);
+            for (; ok && k < kmax && k < presync; k += K / 2) ok = super_step<kPred, K / 2>(k, pre);
         }
         // From here every state of every unit is exact, so a unit that has
         // decoded its own groups may run on into the groups below: it stores
@@ -630,26 +701,18 @@ struct PairDecoder {
         bool run_on = !p.partitioned && k <= kmin && top_min + 1 >= kend;
         run_on = run_on && __ballot(vres + vfq * (int32_t)C < (int32_t)((kend - k) * W)) == 0;
         tready = 0;
-        if (run_on) {
-            for (; ok && k < kmax; k += K) {
-                if (8 * k > thr) {
-                    --level;
-                    thr = level ? thr + (prio_cut(level + 1) - prio_cut(level)) * q : 0xFFFFFFFFu;
-                    set_priority(level);
-                }
-                ok = super_step<kFast>(k, kend);
+        const uint32_t fend = run_on ? kend : kmin;
+        const uint32_t fast_end = run_on ? kmax : kmin - min(kmin, K - 1u);   // last start, plus one
+        pre = fetch(max(vfq - 1, 0));
+        for (; ok && k < fast_end; k += K) {
+            if (8 * k > thr) {
+                --level;
+                thr = level ? thr + (prio_cut(level + 1) - prio_cut(level)) * q : 0xFFFFFFFFu;
+                set_priority(level);
             }
-        } else {
-            for (; ok && k + K <= kmin; k += K) {
-                if (8 * k > thr) {
-                    --level;
-                    thr = level ? thr + (prio_cut(level + 1) - prio_cut(level)) * q : 0xFFFFFFFFu;
-                    set_priority(level);
-                }
-                ok = super_step<kFast>(k, kmin);
-            }
-            for (; ok && k < kmax; k += K) ok = super_step<kPred>(k);
+            ok = super_step<kFast>(k, pre, fend);
         }
+        for (; ok && k < kmax; k += K) ok = super_step<kPred>(k, pre);
         if (!ok && lane == 0) atomicOr(p.err, kDevErrUnderflow);
     }
 };
