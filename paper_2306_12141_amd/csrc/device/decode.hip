@@ -160,9 +160,9 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
         // workgroups would not reach every CU. A 16-wave grid of few pieces puts
         // four waves on each SIMD of a few CUs and leaves the rest idle, while
         // each wave's decode is one latency-bound chain that runs faster with
-        // fewer waves beside it. Up to one run per SIMD the kernel of few.hip
+        // fewer waves beside it. Up to two runs per SIMD the kernel of few.hip
         // decodes it, whose chain is half as long (its 8-byte table and ring
-        // entries leave no room in the LDS for more runs per CU).
+        // entries leave no room in the LDS for more).
         DecodeTuning u = t;
         u.waves = 16;
         DecodeShape s{};
@@ -170,13 +170,14 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
         if (e != hipSuccess) return e;
         const uint64_t pieces = s.units_per_wave ? (s.runs + s.units_per_wave - 1) / s.units_per_wave : 0;
         const uint64_t cus = (uint64_t)device_cus();
-        if (VAR != kAdaptive && s.units_per_wave == 1 && pieces <= kSimdsPerCu * cus) {
+        if (VAR != kAdaptive && s.units_per_wave == 1) {
             DecodeParams q = p;
             q.run = s.units_per_run;
             q.runs = s.runs;
+            FewShape few{};
             hipError_t fe = hipSuccess;
-            if (decode_few(q, W, sizeof(Sym), shape == nullptr, stream, &fe)) {
-                if (shape) *shape = DecodeShape{s.runs, 1u, s.units_per_run, s.runs, 1u};
+            if (decode_few(q, W, sizeof(Sym), few, shape == nullptr, stream, &fe)) {
+                if (shape) *shape = DecodeShape{few.blocks, few.waves, s.units_per_run, s.runs, 1u};
                 return fe;
             }
         }

@@ -1,6 +1,7 @@
-// Decode launches of few runs: one run per workgroup, decoded by its first wave (see
-// few_core.hpp); the other waves only stage the decode table, while the first one
-// fetches its records and its first words.
+// Decode launches of few runs (see few_core.hpp). Up to one run per SIMD: a workgroup per
+// run, decoded by its first wave; the other waves only stage the decode table, while the
+// first one fetches its records and its first words. Up to two per SIMD: a workgroup per
+// CU, whose waves share one table.
 #include "few.hpp"
 
 #include "few_core.hpp"
@@ -11,21 +12,25 @@ namespace {
 
 using namespace dev;
 
-constexpr uint32_t kThreads = 256;
 constexpr uint32_t kLdsBytes = 160u << 10;   // per CU
 // Groups of a run from which super-steps of 16 groups pay: 8-group ones round a run up by
 // less and start sooner (1 MiB at W = 32 in 256 units, 128 groups each: 12.9 against
 // 14.4 us), 16-group ones cost less per group (64 MiB in 256 units, 8192 groups each: 547
 // against 614 us).
 constexpr uint32_t kLongRun = 256;
+constexpr int kRing = 3;                     // chunks of a ring
+
+// Decoding waves of a workgroup, and its threads.
+constexpr int kShared = 8;
+template <int WAVES>
+constexpr uint32_t kThreads = WAVES == 1 ? 256 : 64 * WAVES;
 
 template <typename Sym, bool WIDE>
-__device__ inline void stage_table(const DecodeParams &p, uint32_t lut, uint32_t tid) {
-    constexpr uint32_t kStagers = kThreads - 64;
+__device__ inline void stage_table(const DecodeParams &p, uint32_t lut, uint32_t tid, uint32_t threads) {
     const u32x4 *src = static_cast<const u32x4 *>(p.lut);
     const uint32_t chunks = p.lut_bytes / 16;
 #pragma unroll 6
-    for (uint32_t i = tid; i < chunks; i += kStagers) {
+    for (uint32_t i = tid; i < chunks; i += threads) {
         const u32x4 v = src[i];
         if constexpr (sizeof(Sym) == 1 && !WIDE) {
             // symbol | f << 8 | (slot - F) << 20  ->  {f | symbol << 24, slot - F}
@@ -44,65 +49,82 @@ __host__ __device__ inline uint32_t table_bytes(uint32_t lut_bytes) {
     return sizeof(Sym) == 1 && !WIDE ? 2 * lut_bytes : lut_bytes;
 }
 
-template <int W, typename Sym, int K, int NCH, bool WIDE, bool COUNT>
-__global__ __launch_bounds__(kThreads) void decode_few_runs(DecodeParams p) {
-    using D = FewDecoder<W, Sym, K, NCH, WIDE, COUNT>;
+template <int W, typename Sym, int K, bool WIDE, bool COUNT, int WAVES>
+__global__ __launch_bounds__(kThreads<WAVES>) void decode_few_runs(DecodeParams p) {
+    using D = FewDecoder<W, Sym, K, kRing, WIDE, COUNT>;
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t lut = lds_addr(smem);
-    D d(p, lut, lut + table_bytes<Sym, WIDE>(p.lut_bytes), threadIdx.x & (W - 1u));
-    uint32_t v[D::FILL][D::D];
     const uint32_t wave = uni(threadIdx.x >> 6);
-    if (wave == 0) {
-        d.records(blockIdx.x);
+    const uint32_t run = blockIdx.x + wave * gridDim.x;
+    const bool decodes = wave < WAVES && run < p.runs;
+    D d(p, lut, lut + table_bytes<Sym, WIDE>(p.lut_bytes) + wave * D::RING_BYTES, threadIdx.x & (W - 1u));
+    uint32_t v[D::FILL][D::D];
+    if (decodes) {
+        d.records(run);
         d.fill_request(v);
-    } else {
-        stage_table<Sym, WIDE>(p, lut, threadIdx.x - 64);
     }
+    if (WAVES > 1) stage_table<Sym, WIDE>(p, lut, threadIdx.x, kThreads<WAVES>);
+    else if (wave > 0) stage_table<Sym, WIDE>(p, lut, threadIdx.x - 64, kThreads<WAVES> - 64);
     __syncthreads();
-    if (wave != 0) return;                              // the stagers
+    if (!decodes) return;
     if (W < 64 && (threadIdx.x & 63u) >= W) return;     // lanes without a coder
     d.fill_put(v);
     d.run();
 }
 
-template <int W, typename Sym, int K, int NCH, bool WIDE, bool COUNT>
-bool try_launch(const DecodeParams &p, bool launch, hipStream_t stream, hipError_t *e) {
-    const uint32_t lds = table_bytes<Sym, WIDE>(p.lut_bytes) + FewDecoder<W, Sym, K, NCH, WIDE, COUNT>::RING_BYTES;
-    const uint32_t cus = (uint32_t)device_cus(), per_cu = (p.runs + cus - 1) / cus;
+template <int W, typename Sym, int K, bool WIDE, bool COUNT, int WAVES>
+bool try_launch(const DecodeParams &p, const FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
+    const uint32_t lds = table_bytes<Sym, WIDE>(p.lut_bytes) + WAVES * FewDecoder<W, Sym, K, kRing, WIDE, COUNT>::RING_BYTES;
+    const uint32_t cus = (uint32_t)device_cus(), per_cu = (shape.blocks + cus - 1) / cus;
     if (lds * per_cu > kLdsBytes) return false;
     if (launch) {
-        hipLaunchKernelGGL((decode_few_runs<W, Sym, K, NCH, WIDE, COUNT>), dim3(p.runs), dim3(kThreads), lds, stream, p);
+        hipLaunchKernelGGL((decode_few_runs<W, Sym, K, WIDE, COUNT, WAVES>), dim3(shape.blocks), dim3(kThreads<WAVES>), lds,
+                           stream, p);
         *e = hipGetLastError();
     }
     return true;
 }
 
 // The largest rings that leave every run resident (a run that has to wait for another
-// doubles the launch): with 32 KiB of table (8-byte entries at n = 12) four runs per CU
-// have 8 KiB each, the 4-group rings.
-template <int W, typename Sym, bool WIDE, bool COUNT>
-bool pick(const DecodeParams &p, bool launch, hipStream_t stream, hipError_t *e) {
+// doubles the launch): with 32 KiB of table (8-byte entries at n = 12) four runs per CU in
+// workgroups of their own have 8 KiB each, the 4-group rings.
+template <int W, typename Sym, bool WIDE, bool COUNT, int WAVES>
+bool pick(const DecodeParams &p, const FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
     const uint64_t groups = p.n_symbols / W / p.runs;   // of a run
-    if (groups >= kLongRun && try_launch<W, Sym, 16, 3, WIDE, COUNT>(p, launch, stream, e)) return true;
-    return try_launch<W, Sym, 8, 3, WIDE, COUNT>(p, launch, stream, e) ||
-           try_launch<W, Sym, 4, 3, WIDE, COUNT>(p, launch, stream, e);
+    if (groups >= kLongRun && try_launch<W, Sym, 16, WIDE, COUNT, WAVES>(p, shape, launch, stream, e)) return true;
+    return try_launch<W, Sym, 8, WIDE, COUNT, WAVES>(p, shape, launch, stream, e) ||
+           try_launch<W, Sym, 4, WIDE, COUNT, WAVES>(p, shape, launch, stream, e);
+}
+
+template <int W, typename Sym, bool WIDE, bool COUNT>
+bool pick_waves(const DecodeParams &p, const FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
+    return shape.waves == 1 ? pick<W, Sym, WIDE, COUNT, 1>(p, shape, launch, stream, e)
+                            : pick<W, Sym, WIDE, COUNT, kShared>(p, shape, launch, stream, e);
 }
 
 template <int W, typename Sym>
-bool pick_variant(const DecodeParams &p, bool launch, hipStream_t stream, hipError_t *e) {
-    if (p.quant_bits > 12) return !p.counts && pick<W, Sym, true, false>(p, launch, stream, e);
-    return p.counts ? pick<W, Sym, false, true>(p, launch, stream, e) : pick<W, Sym, false, false>(p, launch, stream, e);
+bool pick_variant(const DecodeParams &p, const FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
+    if (p.quant_bits > 12) return !p.counts && pick_waves<W, Sym, true, false>(p, shape, launch, stream, e);
+    return p.counts ? pick_waves<W, Sym, false, true>(p, shape, launch, stream, e)
+                    : pick_waves<W, Sym, false, false>(p, shape, launch, stream, e);
 }
 
 }  // namespace
 
-bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, bool launch, hipStream_t stream,
-                hipError_t *e) {
-    if (p.tidx || p.runs == 0) return false;
-    if (lanes == 32) return symbol_bytes == 1 ? pick_variant<32, uint8_t>(p, launch, stream, e)
-                                              : pick_variant<32, uint16_t>(p, launch, stream, e);
-    if (lanes == 64) return symbol_bytes == 1 ? pick_variant<64, uint8_t>(p, launch, stream, e)
-                                              : pick_variant<64, uint16_t>(p, launch, stream, e);
+bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, FewShape &shape, bool launch,
+                hipStream_t stream, hipError_t *e) {
+    constexpr uint32_t kSimds = 4;   // per CU
+    const uint32_t cus = (uint32_t)device_cus();
+    // Two runs per SIMD still run at almost the pace of one (64 MiB at W = 32 in 2048 units:
+    // 117 us with the throughput kernel, 82 us here); four do not (4096 units: 70 against
+    // 73 us, the rings are then down to 4 groups).
+    if (p.tidx || p.runs == 0 || p.runs > 2 * kSimds * cus) return false;
+    shape = p.runs <= kSimds * cus ? FewShape{p.runs, 1} : FewShape{cus, (uint32_t)kShared};
+    static_assert(kShared == 2 * kSimds, "a workgroup per CU holds two runs per SIMD");
+    if (lanes == 32) return symbol_bytes == 1 ? pick_variant<32, uint8_t>(p, shape, launch, stream, e)
+                                              : pick_variant<32, uint16_t>(p, shape, launch, stream, e);
+    if (lanes == 64) return symbol_bytes == 1 ? pick_variant<64, uint8_t>(p, shape, launch, stream, e)
+                                              : pick_variant<64, uint16_t>(p, shape, launch, stream, e);
     return false;
 }
 

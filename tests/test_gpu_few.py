@@ -67,3 +67,21 @@ def test_few_runs_word_rate(rc, W, dt, n, A, M):
     blob = rc.encode(s, lanes=W, quant_bits=n, splits=M, alphabet=A, freq=f)
     assert np.array_equal(gpu_decode(rc, blob), s)
 
+
+
+@pytest.mark.parametrize("W,dt,n,N,M", [
+    (32, np.uint8, 12, 3_000_017, 1500), (32, np.uint8, 9, 64 * 2048 * 40, 1025), (64, np.uint16, 12, 3_000_003, 2048),
+    (64, np.uint8, 16, 4_000_001, 1100), (32, np.uint8, 11, 1025 * 32 * 300, 1025)])
+def test_two_runs_per_simd(rc, W, dt, n, N, M):
+    """More runs than SIMDs and up to twice as many: one workgroup per CU, eight runs in
+    each, some with waves that have none."""
+    _say("case two runs per SIMD", W, np.dtype(dt).name, n, N, M)
+    A = 256 if dt == np.uint8 else 4096
+    s = _syms(6500 + M, N, A, dt, 1.1)
+    blob = rc.encode(s, lanes=W, quant_bits=n, splits=M, alphabet=A)
+    sh = rc.Plan(blob).shape()
+    assert sh.runs == blob.splits and _simds() < sh.runs <= 2 * _simds()
+    assert (sh.blocks, sh.waves_per_block, sh.units_per_wave) == (_simds() // 4, 8, 1)
+    assert np.array_equal(gpu_decode(rc, blob), s)
+    part = rc.encode_partitioned(s, lanes=W, quant_bits=n, partitions=M, alphabet=A)
+    assert np.array_equal(gpu_decode(rc, part), s)
