@@ -134,13 +134,19 @@ hipError_t launch_ss(const DecodeParams &p, const DecodeTuning &t, uint32_t resi
     return hipGetLastError();
 }
 
+constexpr uint32_t kSingleWaves = 16;   // waves per CU up to which W = 32 runs are decoded one per wave
+
 template <int W, typename Sym, int K, int WAVES, int VAR>
 hipError_t launch_units(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
     if constexpr (W == 32) {
-        // One unit per wave when every run then has a wave of its own: the
-        // pair kernel would leave half of those waves idle.
+        // One unit per wave while every run then has a wave of its own on half of
+        // the chip's wave slots: the pair kernel would leave half of those waves
+        // idle. Beyond, the pairs (two units per instruction) are worth more than
+        // the waves: 8192 units at W = 32, 64 MiB of bytes 50.4 us one by one and
+        // 45.0 us in pairs, 32 Mi 16-bit symbols 34.8 and 29.0, n = 16 68 and 57;
+        // 3000 units 87.8 and 86.5.
         const uint32_t rs = resident_blocks<32, Sym, K, WAVES, 1, VAR>(p, t);
-        const uint64_t slots = (uint64_t)rs * WAVES;
+        const uint64_t slots = std::min<uint64_t>((uint64_t)rs * WAVES, (uint64_t)kSingleWaves * device_cus());
         const uint32_t k = t.units_per_run && !p.partitioned ? std::min(t.units_per_run, std::max(p.units, 1u)) : 1u;
         const uint64_t runs = ((uint64_t)p.units + k - 1) / k;
         if (rs > 0 && runs <= slots) return launch_ss<32, Sym, K, WAVES, 1, VAR>(p, t, rs, stream, shape);

@@ -85,3 +85,17 @@ def test_two_runs_per_simd(rc, W, dt, n, N, M):
     assert np.array_equal(gpu_decode(rc, blob), s)
     part = rc.encode_partitioned(s, lanes=W, quant_bits=n, partitions=M, alphabet=A)
     assert np.array_equal(gpu_decode(rc, part), s)
+
+
+@pytest.mark.parametrize("dt,n", [(np.uint8, 12), (np.uint16, 12), (np.uint8, 16)])
+def test_pairs_from_half_the_wave_slots(rc, dt, n):
+    """W = 32: one unit per wave up to 16 waves per CU, pairs beyond, exact on both sides."""
+    A = 256 if dt == np.uint8 else 4096
+    s = _syms(6600, 3_000_017, A, dt, 1.1)
+    slots = 4 * _simds()
+    for M, per_wave in ((slots, 1), (slots + 1, 2), (slots + 2, 2)):
+        _say("case pairs", np.dtype(dt).name, n, M)
+        blob = rc.encode(s, lanes=32, quant_bits=n, splits=M, alphabet=A)
+        assert blob.splits == M and rc.Plan(blob).shape().units_per_wave == per_wave
+        assert np.array_equal(gpu_decode(rc, blob), s)
+        assert np.array_equal(gpu_decode(rc, rc.encode_partitioned(s, lanes=32, quant_bits=n, partitions=M, alphabet=A)), s)
