@@ -49,8 +49,12 @@ recoil_status recoil_batch_get_tuning(const recoil_batch *batch, recoil_tuning *
 
 /* One persistent launch per decode-table class that has streams (tables up to
  * 16 KiB, i.e. uint8 with n <= 12; larger tables), each with LDS for its own
- * class's largest table, in that order; a one-thread kernel resets the class's
- * queue counter in the workspace before each. d_out: output base (>= output_bytes);
+ * class's largest table, in that order; one for both where the larger tables take
+ * no workgroup from a CU. Where a launch has more items than resident workgroups, a
+ * one-thread kernel resets the class's queue counter in the workspace before it.
+ * units_per_run = 0 in the tuning: every split point is used, and a batch that
+ * would leave workgroups without an item gets smaller items than
+ * waves x pairs_per_wave pairs. d_out: output base (>= output_bytes);
  * d_error: zeroed device word (RECOIL_DEVERR_* bits). Enqueue-only, capturable.
  * Errors: INVALID_ARG, HIP. */
 recoil_status recoil_decode_batch(const recoil_batch *batch, void *d_workspace, void *d_out, uint32_t *d_error,

@@ -2,8 +2,10 @@
 // tables, uint8 or uint16 symbols, W = 32 or 64) decoded by one launch.
 //
 // Host planning cuts every stream into work items (runs of consecutive unit
-// pairs of one stream) and orders them largest stream first. Each persistent
-// workgroup pops an item from a device counter, restages the decode table in
+// pairs of one stream) and orders them largest stream first. With no more items
+// than resident workgroups each workgroup decodes the one at its position.
+// Otherwise each persistent workgroup pops an item from a device counter. It
+// restages the decode table in
 // LDS only when the item belongs to a different stream than its previous item,
 // and its waves decode the item's pairs with the same per-pair decoder as the
 // single-stream kernel. The queue head lives in device memory and is reset by
@@ -25,13 +27,29 @@ namespace {
 
 using namespace dev;
 
-template <int W, typename Sym, int K, int SS = 64 / W, int VAR = kPlain>
-__device__ inline void run_item(const DecodeParams &p, uint32_t ring0,
-                                uint32_t lane, uint32_t wave, uint32_t waves, uint32_t first, uint32_t count) {
-    PairDecoder<W, Sym, K, SS, VAR> d(p, ring0, lane);
-    const uint32_t share = wave < count ? (count - 1 - wave) / waves + 1 : 0u;
+// Pairs first .. first + count - 1 of one stream. The waves request their first pairs'
+// records and words, then the workgroup stages the stream's decode table (chunks 16-byte
+// pieces; 0: it is the one staged last), so that the three latencies overlap.
+template <int W, typename Sym, int K, int SS, int VAR, int WAVES>
+__device__ inline void run_item(const DecodeParams &p, uint32_t ring0, uint32_t wave, const WorkItem &wi,
+                                unsigned char *lut, uint32_t chunks) {
+    const uint32_t lane = threadIdx.x & 63u, first = wi.first, count = wi.count;
+    using D = PairDecoder<W, Sym, K, SS, VAR>;
+    D d(p, ring0, lane & (W * SS - 1u));
+    typename D::First f;
+    bool any = false;
+    if (wave < count) any = d.request(first + wave, f);
+    const uint4 *src = static_cast<const uint4 *>(p.lut);
+    for (uint32_t i = threadIdx.x; i < chunks; i += 64 * WAVES) reinterpret_cast<uint4 *>(lut)[i] = src[i];
+    __syncthreads();
+    if (W * SS < 64 && lane >= (uint32_t)(W * SS)) return;   // lanes without a coder wait at the item's end
+    const uint32_t share = wave < count ? (count - 1 - wave) / WAVES + 1 : 0u;
     uint32_t left = share;
-    for (uint32_t q = first + wave; q < first + count; q += waves) d.run(q, --left, share);
+    for (uint32_t q = wave; q < count; any = q < count && d.request(first + q, f)) {
+        --left;
+        if (any) d.run(f, left, share);
+        q += WAVES;
+    }
 }
 
 // VAR: kPlain (one-level tables, n <= 12) or kWide (two-level, 13 <= n <= 16), one
@@ -44,26 +62,24 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(RECOIL_S
     unsigned char *lut = smem;
     const uint32_t base = lds_addr(smem) + bp.lut_bytes;   // the pad, whose first word holds the popped item
     const uint32_t wave = uni(threadIdx.x >> 6);
-    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t ring0 = base + L::PAD + wave * L::WAVE_LDS;
     int32_t cur = -1;
     for (;;) {
-        if (threadIdx.x == 0) lds_st<uint32_t>(base, atomicAdd(bp.head, 1u));
-        __syncthreads();
-        const uint32_t it = uni(lds_ld<uint32_t>(base));
+        // No more items than workgroups: one each, without a queue.
+        uint32_t it = blockIdx.x;
+        if (bp.head) {
+            if (threadIdx.x == 0) lds_st<uint32_t>(base, atomicAdd(bp.head, 1u));
+            __syncthreads();
+            it = uni(lds_ld<uint32_t>(base));
+        }
         if (it >= bp.n_items) break;
         const WorkItem wi = uni_load(bp.items + it);
         const StreamDesc d = uni_load(bp.streams + wi.stream);
-        if ((int32_t)wi.stream != cur) {
-            const uint32_t chunks = d.lut_chunks;
-            const uint4 *src = reinterpret_cast<const uint4 *>(bp.ws + d.lut_off);
-            for (uint32_t i = threadIdx.x; i < chunks; i += 64 * WAVES) reinterpret_cast<uint4 *>(lut)[i] = src[i];
-            cur = (int32_t)wi.stream;
-        }
-        __syncthreads();
+        const uint32_t chunks = (int32_t)wi.stream != cur ? d.lut_chunks : 0u;
+        cur = (int32_t)wi.stream;
         DecodeParams p;
         p.words = reinterpret_cast<const uint16_t *>(bp.ws + d.words_off);
-        p.lut = nullptr;
+        p.lut = bp.ws + d.lut_off;
         p.counts = nullptr;
         p.tidx = nullptr;
         p.tables = 1;
@@ -87,19 +103,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(RECOIL_S
                 else static_cast<uint16_t *>(p.out)[i] = (uint16_t)d.fill_symbol;
             }
         } else if (d.lanes == 32) {
-            if (single) {
-                if (lane < 32) {   // one unit per wave: the upper half-wave idles until the item ends
-                    if (d.symbol_bytes == 1) run_item<32, uint8_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
-                    else run_item<32, uint16_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
-                }
+            if (single) {   // one unit per wave, the upper half-wave idle
+                if (d.symbol_bytes == 1) run_item<32, uint8_t, K, 1, VAR, WAVES>(p, ring0, wave, wi, lut, chunks);
+                else run_item<32, uint16_t, K, 1, VAR, WAVES>(p, ring0, wave, wi, lut, chunks);
             } else if (d.symbol_bytes == 1) {
-                run_item<32, uint8_t, K, 2, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
+                run_item<32, uint8_t, K, 2, VAR, WAVES>(p, ring0, wave, wi, lut, chunks);
             } else {
-                run_item<32, uint16_t, K, 2, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
+                run_item<32, uint16_t, K, 2, VAR, WAVES>(p, ring0, wave, wi, lut, chunks);
             }
         } else {
-            if (d.symbol_bytes == 1) run_item<64, uint8_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
-            else run_item<64, uint16_t, K, 1, VAR>(p, ring0, lane, wave, WAVES, wi.first, wi.count);
+            if (d.symbol_bytes == 1) run_item<64, uint8_t, K, 1, VAR, WAVES>(p, ring0, wave, wi, lut, chunks);
+            else run_item<64, uint16_t, K, 1, VAR, WAVES>(p, ring0, wave, wi, lut, chunks);
         }
         if (bp.remaining) {
             // Publish the stream's completion once its last item is done: every
@@ -113,9 +127,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(RECOIL_S
                 __hip_atomic_store(bp.host_done + wi.stream, kHostDone | e, __ATOMIC_RELEASE,
                                    __HIP_MEMORY_SCOPE_SYSTEM);
             }
-        } else {
+        } else if (bp.head) {
             __syncthreads();   // every wave is done with this table before the next item may replace it
         }
+        if (!bp.head) break;
     }
 }
 
@@ -144,9 +159,11 @@ hipError_t launch_var(const BatchParams &bp, uint32_t blocks_per_cu, hipStream_t
     if (per_cu < 1) return hipErrorInvalidConfiguration;
     if (blocks_per_cu > 0) per_cu = std::min<int>(per_cu, (int)blocks_per_cu);
     const uint32_t blocks = std::max<uint32_t>(1, std::min<uint32_t>(bp.n_items, (uint32_t)(cus * per_cu)));
-    hipLaunchKernelGGL(reset_head, dim3(1), dim3(64), 0, stream, bp.head);
+    BatchParams q = bp;
+    if (bp.n_items <= blocks) q.head = nullptr;   // all resident at once: nothing to queue, no reset launch
+    else hipLaunchKernelGGL(reset_head, dim3(1), dim3(64), 0, stream, bp.head);
     const size_t lds = batch_lds<K, WAVES>(bp.lut_bytes);
-    hipLaunchKernelGGL((decode_batch<K, WAVES, VAR>), dim3(blocks), dim3(64 * WAVES), lds, stream, bp);
+    hipLaunchKernelGGL((decode_batch<K, WAVES, VAR>), dim3(blocks), dim3(64 * WAVES), lds, stream, q);
     return hipGetLastError();
 }
 

@@ -41,7 +41,7 @@ struct BatchParams {
     unsigned char *out;           // output base
     const StreamDesc *streams;
     const WorkItem *items;
-    uint32_t *head;               // work-queue head (device counter, reset before each launch)
+    uint32_t *head;               // work-queue head (device counter, reset before each launch that uses it)
     uint32_t *err;                // error word(s): err[stream * err_stride]
     uint32_t n_items;
     uint32_t lut_bytes;           // LDS bytes reserved for the largest table in the batch

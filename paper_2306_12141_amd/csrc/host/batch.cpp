@@ -55,19 +55,69 @@ uint32_t pairs_of(const PlanData &pl, uint32_t k) {
     return W == 32 ? (runs + 1) / 2 : runs;
 }
 
-// Units per run of one stream: the tuned length, shortened for a stream with too
+// What the launch does with a batch as a whole.
+struct BatchShape {
+    uint32_t run = 1;        // units per run, before a stream's own limits (units_per_run; 0: 1)
+    uint32_t per_item = 1;   // pairs of a work item
+    bool single = false;     // every W = 32 unit on a wave of its own
+};
+
+// units_per_run = 0 leaves the shape to the batch's size; otherwise it is the tuning's.
+//
+// Every split point is used. Items are waves x pairs_per_wave pairs, or fewer, so that a
+// batch of less work than that is spread over all workgroups that the chip holds instead of
+// a few full ones, each item on a workgroup of its own: 60 streams of 4 KiB .. 16 MiB, two
+// launches of 173 and 66 items of 32 pairs 191 us, one of 495 items of 13 pairs 99 us; 24
+// streams up to 1 MiB 56 and 17 us, 40 up to 4 MiB 302 and 109. (300 streams, 105 pairs for
+// each workgroup: items of 16 or 32 pairs 348 and 353 us, runs of two units 358 and 375.)
+// W = 32 units are decoded one per wave while that takes at most half of the wave slots, as
+// for one stream.
+BatchShape batch_shape(const BatchData &b) {
+    const recoil_tuning &t = b.tuning;
+    BatchShape sh;
+    sh.per_item = std::max(1u, t.waves * t.pairs_per_wave);
+    sh.run = std::max(1u, t.units_per_run);
+    if (t.units_per_run != 0) return sh;
+    const uint64_t cus = device_cus() > 1 ? (uint64_t)device_cus() : 256u;
+    constexpr uint64_t kWavesPerCu = 32;
+    std::vector<uint32_t> units, pairs;   // of each stream, every split point used
+    uint64_t all_units = 0, all_pairs = 0;
+    for (const PlanData &pl : b.plans) {
+        if (pl.single_symbol || pl.blob->n_symbols == 0) continue;
+        const uint32_t M = pl.blob->splits();
+        units.push_back(M);
+        pairs.push_back(M <= t.waves ? M : pairs_of(pl, 1));   // (few units: one per wave, see build_items)
+        all_units += M;
+        all_pairs += pairs.back();
+    }
+    const uint64_t slots = cus * kWavesPerCu, workgroups = std::max<uint64_t>(1, slots / t.waves);
+    sh.single = all_units <= slots / 2;
+    const std::vector<uint32_t> &work = sh.single ? units : pairs;
+    const uint64_t total = sh.single ? all_units : all_pairs;
+    if (total > workgroups * sh.per_item) return sh;
+    uint32_t fine = (uint32_t)std::max<uint64_t>(1, (total + workgroups - 1) / workgroups);
+    for (; fine < sh.per_item; ++fine) {   // all items resident at once, the streams' last ones included
+        uint64_t n = 0;
+        for (uint32_t w : work) n += (w + fine - 1) / fine;
+        if (n <= workgroups) break;
+    }
+    sh.per_item = std::min(sh.per_item, fine);
+    return sh;
+}
+
+// Units per run of one stream: the batch's length, shortened for a stream with too
 // few units to give each unit slot of a workgroup (waves x units per wave) a run
 // of that length, so that its units spread over the waves instead of leaving
 // some idle while others decode long runs.
-uint32_t stream_run(const PlanData &pl, const recoil_tuning &t) {
+uint32_t stream_run(const PlanData &pl, const recoil_tuning &t, uint32_t run) {
     const uint32_t M = pl.blob->splits();
     if (pl.blob->partitioned()) return 1;   // independent sub-sequences: one unit per run
     const uint32_t slots = std::max(1u, t.waves * (pl.blob->lanes == 32 ? 2u : 1u));
     const uint32_t spread = std::max(1u, (M + slots - 1) / slots);
-    return run_of(M, std::min(std::max(t.units_per_run, 1u), spread));
+    return run_of(M, std::min(run, spread));
 }
 
-// Work items: per stream, waves * pairs_per_wave consecutive pairs each; streams
+// Work items: per stream, per_item consecutive pairs each; streams
 // in decreasing size so the longest work starts first.
 void build_items(BatchData &b) {
     b.items.clear();
@@ -79,7 +129,7 @@ void build_items(BatchData &b) {
         return b.plans[a].blob->n_symbols * b.plans[a].blob->symbol_bytes >
                b.plans[c].blob->n_symbols * b.plans[c].blob->symbol_bytes;
     });
-    const uint32_t per_item = std::max(1u, b.tuning.waves * b.tuning.pairs_per_wave);
+    const BatchShape sh = batch_shape(b);
     for (uint32_t c = 0; c < kBatchClasses; ++c) { b.cls_begin[c] = 0; b.cls_count[c] = 0; b.cls_lut[c] = 0; }
     for (uint32_t s : order) {
         const PlanData &pl = b.plans[s];
@@ -91,14 +141,15 @@ void build_items(BatchData &b) {
         if (pl.single_symbol) {
             b.items.push_back({s, 0, 1, 1});
         } else {
-            const uint32_t run = stream_run(pl, b.tuning);
+            const uint32_t run = stream_run(pl, b.tuning, sh.run);
             // A W = 32 stream with no more runs than a workgroup has waves decodes one
             // unit per wave (each run a wave of its own, not half of one).
             const uint32_t M = pl.blob->splits(), runs = (M + run - 1) / run;
-            const bool single = pl.blob->lanes == 32 && runs <= b.tuning.waves;
+            const bool single = pl.blob->lanes == 32 && (sh.single || runs <= b.tuning.waves);
             const uint32_t pairs = single ? runs : pairs_of(pl, run);
             const uint32_t tag = run | (single ? kItemSingle : 0u);
-            for (uint32_t f = 0; f < pairs; f += per_item) b.items.push_back({s, f, std::min(per_item, pairs - f), tag});
+            for (uint32_t f = 0; f < pairs; f += sh.per_item)
+                b.items.push_back({s, f, std::min(sh.per_item, pairs - f), tag});
         }
         b.cls_count[c] += (uint32_t)(b.items.size() - before);
     }
@@ -111,7 +162,8 @@ bool tuning_ok(const recoil_tuning &t) {
 
 BatchTuning device_tuning(const recoil_tuning &t) { return BatchTuning{t.waves, t.chunk_groups, t.blocks_per_cu}; }
 
-BatchParams params_of(const BatchData &b, uint32_t cls, void *d_ws, void *d_out, uint32_t *d_err) {
+// A launch: the items of class cls, and with joined set those of the next class too.
+BatchParams params_of(const BatchData &b, uint32_t cls, bool joined, void *d_ws, void *d_out, uint32_t *d_err) {
     BatchParams bp{};
     unsigned char *ws = static_cast<unsigned char *>(d_ws);
     bp.ws = ws;
@@ -120,18 +172,28 @@ BatchParams params_of(const BatchData &b, uint32_t cls, void *d_ws, void *d_out,
     bp.items = reinterpret_cast<const WorkItem *>(ws + b.off_items) + b.cls_begin[cls];
     bp.head = reinterpret_cast<uint32_t *>(ws + b.off_head + cls * kHeadStride);
     bp.err = d_err;
-    bp.n_items = b.cls_count[cls];
-    bp.lut_bytes = b.cls_lut[cls];
+    bp.n_items = b.cls_count[cls] + (joined ? b.cls_count[cls + 1] : 0u);
+    bp.lut_bytes = joined ? std::max(b.cls_lut[cls], b.cls_lut[cls + 1]) : b.cls_lut[cls];
     bp.wide = cls == kWideClass ? 1u : 0u;
     return bp;
 }
 
-// One persistent launch per table class that has work, in class order.
-hipError_t launch_classes(const BatchData &b, void *d_ws, void *d_out, uint32_t *d_err, hipStream_t stream) {
+// One persistent launch per table class that has work, in class order; classes 0 and 1
+// in one if the larger tables leave as many workgroups per CU (4-group rings do): the
+// classes' last items then overlap. heads: queue heads kHeadStride bytes apart (NULL: the
+// workspace's).
+hipError_t launch_classes(const BatchData &b, void *d_ws, void *d_out, uint32_t *d_err, unsigned char *heads,
+                          hipStream_t stream) {
+    const BatchTuning t = device_tuning(b.tuning);
     for (uint32_t c = 0; c < kBatchClasses; ++c) {
         if (b.cls_count[c] == 0) continue;
-        hipError_t e = launch_batch(params_of(b, c, d_ws, d_out, d_err), device_tuning(b.tuning), stream);
+        const bool joined = c == 0 && b.cls_count[1] != 0 &&
+                            batch_blocks_per_cu(t, std::max(b.cls_lut[0], b.cls_lut[1])) == batch_blocks_per_cu(t, b.cls_lut[0]);
+        BatchParams bp = params_of(b, c, joined, d_ws, d_out, d_err);
+        if (heads) bp.head = reinterpret_cast<uint32_t *>(heads + c * kHeadStride);
+        const hipError_t e = launch_batch(bp, t, stream);
         if (e != hipSuccess) return e;
+        if (joined) ++c;
     }
     return hipSuccess;
 }
@@ -185,6 +247,14 @@ recoil_status recoil_batch_create(const recoil_blob *const *blobs, uint32_t coun
     // Item capacity: the finest tuning (8 waves, one pair per wave).
     size_t cap = 0;
     for (const PlanData &pl : b.plans) cap += pl.single_symbol ? 1 : (pairs_of(pl, 1) + 7) / 8;
+    // A shape left to the batch's size may be finer still.
+    const recoil_tuning asked = b.tuning;
+    for (uint32_t waves : {8u, 16u}) {
+        b.tuning = recoil_tuning{waves, asked.chunk_groups, 1, 0, 0};
+        build_items(b);
+        cap = std::max(cap, b.items.size());
+    }
+    b.tuning = asked;
     b.items_cap = std::max<size_t>(cap, 1);
     size_t off = 0;
     b.off_head = off;  off = ws_align(off + kBatchHeadBytes);
@@ -306,7 +376,7 @@ recoil_status recoil_decode_batch(const recoil_batch *batch, void *d_ws, void *d
     using namespace recoil;
     if (!batch || !d_ws || !d_out || !d_error) return fail(RECOIL_ERR_INVALID_ARG, "decode_batch: bad arguments");
     const BatchData &b = batch->d;
-    hipError_t e = launch_classes(b, d_ws, d_out, d_error, stream);
+    hipError_t e = launch_classes(b, d_ws, d_out, d_error, nullptr, stream);
     if (e != hipSuccess) return fail(RECOIL_ERR_HIP, std::string("decode_batch: ") + hipGetErrorString(e));
     return RECOIL_OK;
 }
@@ -325,15 +395,10 @@ recoil_status recoil_decode_batch_noalloc(const recoil_batch *batch, const void 
     uint32_t *heads = nullptr;
     hipError_t e = static_scratch(&heads);
     if (e != hipSuccess) return fail(RECOIL_ERR_HIP, std::string("decode_batch_noalloc: ") + hipGetErrorString(e));
-    // The workspace is only read: params_of's head pointer into it is replaced below.
-    void *ws = const_cast<void *>(d_ws);
-    for (uint32_t c = 0; c < kBatchClasses; ++c) {
-        if (b.cls_count[c] == 0) continue;
-        BatchParams bp = params_of(b, c, ws, d_out, d_error);
-        bp.head = heads + c * kStaticHeadStride;
-        e = launch_batch(bp, device_tuning(b.tuning), stream);
-        if (e != hipSuccess) return fail(RECOIL_ERR_HIP, std::string("decode_batch_noalloc: ") + hipGetErrorString(e));
-    }
+    // The workspace is only read.
+    static_assert(kStaticHeadStride * 4 == kHeadStride, "static queue heads as far apart as the workspace's");
+    e = launch_classes(b, const_cast<void *>(d_ws), d_out, d_error, reinterpret_cast<unsigned char *>(heads), stream);
+    if (e != hipSuccess) return fail(RECOIL_ERR_HIP, std::string("decode_batch_noalloc: ") + hipGetErrorString(e));
     return RECOIL_OK;
 }
 
@@ -382,7 +447,7 @@ recoil_status recoil_batch_graph_create(const recoil_batch *batch, void *d_ws, v
     if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         const BatchData &b = batch->d;
-        hipError_t le = launch_classes(b, d_ws, d_out, d_error, cs);
+        hipError_t le = launch_classes(b, d_ws, d_out, d_error, nullptr, cs);
         e = hipStreamEndCapture(cs, &g->graph);
         if (le != hipSuccess) e = le;
     }

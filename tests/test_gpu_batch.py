@@ -305,3 +305,30 @@ def test_batch_with_wide_tables(rc, mixed):
         torch.cuda.synchronize()
         assert int(err.item()) == 0, run
         _check_all(batch, out, streams)
+
+
+@pytest.mark.parametrize("streams,units", [(3, 5), (64, 64), (64, 65), (130, 60), (40, 700)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_batch_item_sizes(rc, streams, units, wide):
+    """Batches around the limits of the default shape: a few items, one unit per wave up to
+    half of the wave slots and pairs beyond, an item for every workgroup, more items than
+    workgroups (the queue); byte and 16-bit streams in one launch, twice in a row."""
+    from paper_2306_12141_amd.batch import Batch
+    from tests.test_gpu_decode import _syms
+    _say("case batch item sizes", streams, units, wide)
+    syms, blobs = [], []
+    for i in range(streams):
+        A, dt = (4096, np.uint16) if wide and i % 3 == 0 else (256, np.uint8)
+        s = _syms(7100 + i, units * 320 + 37 * i, A, dt, 1.1)
+        syms.append(s)
+        blobs.append(rc.encode(s, lanes=64 if i % 5 == 4 else 32, quant_bits=12, splits=units, alphabet=A))
+    batch = Batch(blobs)
+    ws, out, err = batch.allocate()
+    batch.upload(ws)
+    for poison in (0x5A, 0xA5):
+        out.fill_(poison)
+        batch.decode(ws, out, err)
+        torch.cuda.synchronize()
+        assert int(err.item()) == 0
+        for i, s in enumerate(syms):
+            assert np.array_equal(batch.symbols_of(out, i, s.dtype), s), i
