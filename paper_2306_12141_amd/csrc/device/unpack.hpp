@@ -31,13 +31,15 @@ struct UnpackParams {
     uint64_t words;               // B
     uint64_t groups;              // G
     uint64_t eb, eg;              // ceil(B/M), ceil(G/M)
+    uint64_t offset_at, group_at; // bit positions of the two series' first entries
+    uint32_t offset_width, group_width;   // their magnitude widths
     uint32_t splits;              // M of the packed stream
     uint32_t step;
     uint32_t units;               // records written: (M - 1) / step + 1
     uint32_t lanes_per_unit;      // W: 32 or 64
 };
 
-// One 64-lane wave per output unit. Returns hipSuccess or the launch error.
+// W lanes per output unit. Returns hipSuccess or the launch error.
 hipError_t launch_unpack(const UnpackParams &p, hipStream_t stream);
 
 }  // namespace recoil

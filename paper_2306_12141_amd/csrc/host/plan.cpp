@@ -299,6 +299,19 @@ hipError_t enqueue_unpack(const recoil::PlanData &pl, char *base, hipStream_t st
     u.step = pl.step;
     u.units = pl.units;
     u.lanes_per_unit = b.lanes;
+    if (u.splits > 1) {
+        // The series follow each other: a 5-bit width - 1, then per split point a sign
+        // and the magnitude.
+        auto width_at = [&](uint64_t bit) {
+            const uint8_t *q = pl.packed_bits.data() + (bit >> 3);
+            return ((((uint32_t)q[0] << 8 | q[1]) >> (11 - (bit & 7))) & 31u) + 1u;
+        };
+        u.offset_at = 5;
+        u.offset_width = width_at(0);
+        const uint64_t group_field = 5 + (uint64_t)(u.splits - 1) * (1 + u.offset_width);
+        u.group_at = group_field + 5;
+        u.group_width = width_at(group_field);
+    }
     return launch_unpack(u, stream);
 }
 

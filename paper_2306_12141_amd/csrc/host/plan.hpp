@@ -23,7 +23,7 @@ struct PlanData {
     // metadata section (kept split points (u+1) step, Sec. 3.3); meta and lanes stay empty.
     bool packed = false;
     uint32_t step = 1;
-    std::vector<uint8_t> packed_bits;    // the section + 8 zero bytes (the unpacker reads 5-byte windows)
+    std::vector<uint8_t> packed_bits;    // the section + 8 zero bytes (the unpacker reads 8-byte windows)
     std::vector<uint32_t> block_bit;     // M - 1 block bit offsets
     // Workspace layout of a single-stream plan (byte offsets from the workspace base).
     size_t off_words = 0, off_lut = 0, off_meta = 0, off_lanes = 0, total = 0;
