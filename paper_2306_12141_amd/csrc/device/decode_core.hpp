@@ -72,9 +72,9 @@ struct Table<uint8_t> {
         x = __umul24(f, x >> n) + (e >> 20);
         return e;             // the low byte is the symbol
     }
-    // Adaptive coding: the symbol's own table t of the 2^n-entry tables laid end to end.
+    // Adaptive coding: the symbol's own table at LDS address t of the tables laid end to end.
     __device__ static inline uint32_t step_t(uint32_t &x, uint32_t n, uint32_t mask, uint32_t t) {
-        const Entry e = lds_ld<Entry>(((t << n) | (x & mask)) << 2);
+        const Entry e = lds_ld<Entry>(((x & mask) << 2) + t);
         const uint32_t f = (e >> 8) & 0xFFFu;
         x = __umul24(f, x >> n) + (e >> 20);
         return e;
@@ -237,7 +237,7 @@ struct PairDecoder {
     // W = 64 the transpose's seven VALU per four groups cost more than the three
     // stores they save (1 % slower).
     static constexpr bool QUAD = W == 32 && sizeof(Sym) == 1 && K % 4 == 0;
-    static_assert(!ADAPT || sizeof(Sym) == 1, "adaptive decoding reads the table index at the symbol's byte offset");
+    static_assert(!ADAPT || (sizeof(Sym) == 1 && K == 4), "adaptive decoding reads the table indices at the symbols' byte offsets, four groups at a time");
 
     const DecodeParams &p;
     uint32_t ring0;        // LDS address of this wave's first unit
@@ -265,12 +265,8 @@ struct PairDecoder {
     // address at which it wraps, and a mask that confines a read ballot to the
     // lane's own half-wave.
     uint32_t vb, vlim, lowmask;
-    // Adaptive coding: the table indices of the fast super-steps k and k + K (fetched
-    // a super-step ahead; tready: tcur already holds super-step k's). A predicated or
-    // synchronisation super-step fetches its own into tcur at its start (those run
-    // outside the fast loops, so the registers are free then).
-    uint32_t tcur[K], tn1[K];
-    uint32_t tready = 0;
+    // Adaptive coding: the LDS addresses of the super-step's tables.
+    uint32_t tcur[K];
     uint32_t x, rec, act, lim;
     uint32_t my_top, my_ghi, my_steps, lane_off;
     uint32_t quad_off;     // QUAD: this lane's dword offset from the fast body's group pointer, plus 3W
@@ -458,15 +454,29 @@ struct PairDecoder {
         if constexpr (S == 1) a = uni(a);   // no instruction: tells the compiler that the sum is uniform
     }
 
-    // This lane's table indices of the K groups from group top0 - k down (the bytes
-    // at its output offsets; only for groups inside the stream).
-    __device__ inline void load_tidx(uint32_t k, uint32_t (&dst)[K]) const {
-        const uint8_t *b = p.tidx + (uint64_t)(top0 - k) * W + lane_off;
-#pragma unroll
-        for (uint32_t g = 0; g < K; ++g) dst[g] = *(b - (int64_t)(g * W));
+    // The table indices of the four groups of fast super-step k (groups inside the stream):
+    // one dword per lane, lane 4a + b of a quad group b's four of the quad's coders, as
+    // store_quad writes symbols. A super-step's dword is requested two super-steps ahead
+    // (before: a byte per lane and group, one super-step ahead and moved from register to
+    // register at its end, which waited for it and for all stores: 32 Mi symbols 46.0 us,
+    // now 39.4).
+    __device__ inline uint32_t load_tidx(uint32_t k) const {
+        const uint8_t *b = p.tidx + (uint64_t)(top0 - k) * W;
+        uint32_t v;
+        __builtin_memcpy(&v, b + quad_off - 3 * W, 4);
+        return v;
+    }
+    // Byte g of the result: this lane's index of group g (a 4 x 4 byte transpose across the
+    // quad, its columns from the highest coder down).
+    __device__ inline uint32_t spread_tidx(uint32_t v) const {
+        const uint32_t b = lane & 3u;
+        const uint32_t p2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);
+        const uint32_t h = __builtin_amdgcn_perm(p2, v, (b & 2u) ? 0x00010405u : 0x06070203u);
+        const uint32_t p1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)h, 0xB1, 0xF, 0xF, false);
+        return __builtin_amdgcn_perm(p1, h, (b & 1u) ? 0x03070105u : 0x06020400u);
     }
 
-    // The same for KK groups of a predicated or synchronisation super-step, where a
+    // The tables of KK groups of a predicated or synchronisation super-step, where a
     // lane's group may lie outside its unit or the stream: those lanes load nothing.
     template <uint32_t KK>
     __device__ inline void load_tidx_checked(uint32_t k) {
@@ -474,7 +484,7 @@ struct PairDecoder {
         for (uint32_t g = 0; g < KK; ++g) {
             const uint32_t kk = k + g;
             const uint64_t i = (uint64_t)(my_top - kk) * W + coder;
-            tcur[g] = (kk <= my_top && i < p.n_symbols) ? (uint32_t)p.tidx[i] : 0u;
+            tcur[g] = ((kk <= my_top && i < p.n_symbols) ? (uint32_t)p.tidx[i] : 0u) << (n + 2u);
         }
     }
 
@@ -598,12 +608,14 @@ struct PairDecoder {
     // Returns false if a unit read past its first word (corrupt split data).
     // fend: fast super-steps of the current loop are those at k' with k' + K <= fend.
     template <int MODE, uint32_t KK = K>
-    __device__ inline bool super_step(uint32_t k, Chunk &pre, uint32_t fend = 0) {
+    __device__ inline bool super_step(uint32_t k, Chunk &pre, uint32_t fend, uint32_t &tq) {
         if constexpr (ADAPT && MODE == kFast) {
-            // Table indices: this super-step's unless fetched ahead, and the next
-            // one's when it is also fast (its groups are then inside the stream).
-            if (!tready) load_tidx(k, tcur);
-            if (k + 2 * K <= fend) load_tidx(k + K, tn1);
+            // tq: this super-step's table indices; the next but one's are requested into it
+            // when that is also fast (its groups are then inside the stream).
+            const uint32_t t = spread_tidx(tq);
+            if (k + 3 * K <= fend) tq = load_tidx(k + 2 * K);
+#pragma unroll
+            for (uint32_t g = 0; g < K; ++g) tcur[g] = ((t >> (8 * g)) & 0xFFu) << (n + 2u);
         } else if constexpr (ADAPT) {
             load_tidx_checked<KK>(k);
         }
@@ -636,11 +648,6 @@ struct PairDecoder {
                 vpo = vpo == 4 * C ? 0u : vpo + 2 * C;
                 if constexpr (MODE == kFast) pre = fetch(max(vfq - 1, 0));
             }
-        }
-        if constexpr (ADAPT && MODE == kFast) {
-#pragma unroll
-            for (uint32_t g = 0; g < K; ++g) tcur[g] = tn1[g];
-            tready = k + 2 * K <= fend ? 1u : 0u;
         }
         return __ballot(vres < 0) == 0;   // read below the first word: corrupt split data
     }
@@ -676,16 +683,17 @@ struct PairDecoder {
         bool ok = true;
         uint32_t k = 0;
         Chunk pre;
+        uint32_t tq0 = 0, tq1 = 0;   // adaptive coding only
         // The lean body needs every unit within its own groups for the whole
         // lead-in; it does not track which lanes are on, so afterwards (when all
         // are) the flag is set for the predicated body of the end.
         const uint32_t lead = (presync + K / 2 - 1) / (K / 2) * (K / 2);
         if (sync_lean && lead <= kmin) {
             lim = 0;
-            for (; ok && k < presync; k += K / 2) ok = super_step<kSync, K / 2>(k, pre);
+            for (; ok && k < presync; k += K / 2) ok = super_step<kSync, K / 2>(k, pre, 0u, tq0);
             active = true;
         } else {
-            for (; ok && k < kmax && k < presync; k += K / 2) ok = super_step<kPred, K / 2>(k, pre);
+            for (; ok && k < kmax && k < presync; k += K / 2) ok = super_step<kPred, K / 2>(k, pre, 0u, tq0);
         }
         // From here every state of every unit is exact, so a unit that has
         // decoded its own groups may run on into the groups below: it stores
@@ -700,19 +708,35 @@ struct PairDecoder {
         // over into the sub-sequence below.
         bool run_on = !p.partitioned && k <= kmin && top_min + 1 >= kend;
         run_on = run_on && __ballot(vres + vfq * (int32_t)C < (int32_t)((kend - k) * W)) == 0;
-        tready = 0;
         const uint32_t fend = run_on ? kend : kmin;
         const uint32_t fast_end = run_on ? kmax : kmin - min(kmin, K - 1u);   // last start, plus one
         pre = fetch(max(vfq - 1, 0));
-        for (; ok && k < fast_end; k += K) {
+        auto lower_priority = [&]() {
             if (8 * k > thr) {
                 --level;
                 thr = level ? thr + (prio_cut(level + 1) - prio_cut(level)) * q : 0xFFFFFFFFu;
                 set_priority(level);
             }
-            ok = super_step<kFast>(k, pre, fend);
+        };
+        if constexpr (ADAPT) {
+            // Two indices in flight, each in a register of its own.
+            if (k + K <= fend) tq0 = load_tidx(k);
+            if (k + 2 * K <= fend) tq1 = load_tidx(k + K);
+            while (ok && k < fast_end) {
+                lower_priority();
+                ok = super_step<kFast>(k, pre, fend, tq0);
+                k += K;
+                if (!ok || k >= fast_end) break;
+                ok = super_step<kFast>(k, pre, fend, tq1);
+                k += K;
+            }
+        } else {
+            for (; ok && k < fast_end; k += K) {
+                lower_priority();
+                ok = super_step<kFast>(k, pre, fend, tq0);
+            }
         }
-        for (; ok && k < kmax; k += K) ok = super_step<kPred>(k, pre);
+        for (; ok && k < kmax; k += K) ok = super_step<kPred>(k, pre, 0u, tq0);
         if (!ok && lane == 0) atomicOr(p.err, kDevErrUnderflow);
     }
 };

@@ -99,3 +99,29 @@ def test_pairs_from_half_the_wave_slots(rc, dt, n):
         assert blob.splits == M and rc.Plan(blob).shape().units_per_wave == per_wave
         assert np.array_equal(gpu_decode(rc, blob), s)
         assert np.array_equal(gpu_decode(rc, rc.encode_partitioned(s, lanes=32, quant_bits=n, partitions=M, alphabet=A)), s)
+
+
+@pytest.mark.parametrize("W,N,M", [(32, 32 * 4 * 7 + 3, 1), (32, 400_003, 40), (64, 400_001, 40), (32, 3_000_019, 5000),
+                                   (64, 3_000_001, 3000)])
+def test_adaptive_index_blocks(rc, W, N, M):
+    """Table indices are read four groups at a time: lengths around the blocks, one unit, one
+    unit and a pair per wave, an index array that starts at an odd address."""
+    import synth
+    _say("case adaptive index blocks", W, N, M)
+    pmfs, tidx, s = synth.adaptive_stream(66, N)
+    f = np.stack([rc.quantize(np.maximum(np.round(p * 65536), 1).astype(np.uint64), 9) for p in pmfs])
+    blob = rc.encode_adaptive(s, f, tidx, lanes=W, quant_bits=9, splits=M, alphabet=64)
+    plan = rc.Plan(blob)
+    ws = plan.allocate_workspace()
+    plan.upload(ws)
+    buf = torch.zeros(N + 64, dtype=torch.uint8, device="cuda")
+    for off in (0, 1, 3):
+        index = buf[off:off + N]
+        index.copy_(torch.from_numpy(tidx))
+        for poison in (0x5A, 0xA5):
+            out = plan.allocate_output()
+            out.fill_(poison)
+            err = torch.zeros(1, dtype=torch.int32, device="cuda")
+            plan.decode_adaptive(ws, index, out, err)
+            torch.cuda.synchronize()
+            assert int(err.item()) == 0 and np.array_equal(plan.symbols_of(out), s)
