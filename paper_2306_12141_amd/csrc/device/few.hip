@@ -1,7 +1,14 @@
 // Decode launches of few runs (see few_core.hpp). Up to one run per SIMD: a workgroup per
-// run, decoded by its first wave; the other waves only stage the decode table, while the
-// first one fetches its records and its first words. Up to two per SIMD: a workgroup per
-// CU, whose waves share one table.
+// run, decoded by its first wave and supplied with looked-up words by its second; all but
+// the first stage the decode table, while the first one fetches its records and its first
+// words. Up to two per SIMD: a workgroup per CU, whose waves share one table and look their
+// words up themselves (s_barrier, by which a run's two waves meet, is the whole workgroup's).
+//
+// The decoding wave has the higher priority: with four runs on a CU its SIMD also runs
+// another run's helper, which has time (n = 16, 64 MiB at W = 32 in 1024 units: 189 us
+// without, 176 us with; in 512 units at n = 12 210 and 201 us). A run's first wave decodes:
+// on a CU the first waves of workgroups start on different SIMDs; decoding waves chosen by
+// block number met on one (64 MiB at W = 32 in 1024 units: 236 us).
 #include "few.hpp"
 
 #include "few_core.hpp"
@@ -15,8 +22,8 @@ using namespace dev;
 constexpr uint32_t kLdsBytes = 160u << 10;   // per CU
 // Groups of a run from which super-steps of 16 groups pay: 8-group ones round a run up by
 // less and start sooner (1 MiB at W = 32 in 256 units, 128 groups each: 12.9 against
-// 14.4 us), 16-group ones cost less per group (64 MiB in 256 units, 8192 groups each: 547
-// against 614 us).
+// 14.4 us), 16-group ones cost less per group (64 MiB in 256 units, 8192 groups each: 390
+// against 442 us).
 constexpr uint32_t kLongRun = 256;
 constexpr int kRing = 3;                     // chunks of a ring
 
@@ -51,30 +58,38 @@ __host__ __device__ inline uint32_t table_bytes(uint32_t lut_bytes) {
 
 template <int W, typename Sym, int K, bool WIDE, bool COUNT, int WAVES>
 __global__ __launch_bounds__(kThreads<WAVES>) void decode_few_runs(DecodeParams p) {
-    using D = FewDecoder<W, Sym, K, kRing, WIDE, COUNT>;
+    constexpr bool HELP = WAVES == 1;
+    using D = FewDecoder<W, Sym, K, kRing, WIDE, COUNT, HELP>;
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t lut = lds_addr(smem);
     const uint32_t wave = uni(threadIdx.x >> 6);
-    const uint32_t run = blockIdx.x + wave * gridDim.x;
-    const bool decodes = wave < WAVES && run < p.runs;
-    D d(p, lut, lut + table_bytes<Sym, WIDE>(p.lut_bytes) + wave * D::RING_BYTES, threadIdx.x & (W - 1u));
+    const bool helps = HELP && wave == WAVES;
+    const uint32_t slot = helps ? 0u : wave;
+    const uint32_t run = blockIdx.x + slot * gridDim.x;
+    const bool works = slot < WAVES && run < p.runs;
+    D d(p, lut, lut + table_bytes<Sym, WIDE>(p.lut_bytes) + slot * D::RING_BYTES, threadIdx.x & (W - 1u));
     uint32_t v[D::FILL][D::D];
-    if (decodes) {
+    if (works) {
         d.records(run);
-        d.fill_request(v);
+        d.fill_request(v, helps);
     }
     if (WAVES > 1) stage_table<Sym, WIDE>(p, lut, threadIdx.x, kThreads<WAVES>);
     else if (wave > 0) stage_table<Sym, WIDE>(p, lut, threadIdx.x - 64, kThreads<WAVES> - 64);
     __syncthreads();
-    if (!decodes) return;
+    if (!works) return;     // (s_barrier does not wait for waves that have ended)
     if (W < 64 && (threadIdx.x & 63u) >= W) return;     // lanes without a coder
-    d.fill_put(v);
-    d.run();
+    d.fill_put(v, helps);
+    if (helps) {
+        d.supply();
+    } else {
+        if (HELP) __builtin_amdgcn_s_setprio(3);
+        d.run();
+    }
 }
 
 template <int W, typename Sym, int K, bool WIDE, bool COUNT, int WAVES>
 bool try_launch(const DecodeParams &p, const FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
-    const uint32_t lds = table_bytes<Sym, WIDE>(p.lut_bytes) + WAVES * FewDecoder<W, Sym, K, kRing, WIDE, COUNT>::RING_BYTES;
+    const uint32_t lds = table_bytes<Sym, WIDE>(p.lut_bytes) + WAVES * FewDecoder<W, Sym, K, kRing, WIDE, COUNT, WAVES == 1>::RING_BYTES;
     const uint32_t cus = (uint32_t)device_cus(), per_cu = (shape.blocks + cus - 1) / cus;
     if (lds * per_cu > kLdsBytes) return false;
     if (launch) {

@@ -15,15 +15,16 @@
 // an address (ring or table) and a factor (x << (16 - n) or x >> n) while the offset of
 // its word is being counted, and a group needs one LDS read and one multiply-add after
 // it. The look-up of the words (one table read per word, 0.3-0.7 words per symbol) runs
-// off the chain, when a chunk is put into the ring.
+// off the chain, when a chunk is put into the ring: up to one run per SIMD on another
+// wave (HELP), which costs the decoding wave one meeting per super-step.
 //
-// What bounds it: the chain, about 50 ns per group (mad, compare, count, address, select,
-// 8 cycles each for a lone wave, and an LDS read of 44), plus the look-ups, 9 ns per group
-// at 0.36 words per symbol. Measured before (the throughput kernel, one wave per
-// workgroup) and after: 64 MiB of bytes at W = 32 in 256 units 883 -> 525 us, in 1024
-// units 225 -> 134 us; at W = 64 in 256 units 406 -> 235 us; 1 MiB at W = 32 in 256 units
-// 18.9 -> 12.6 us; 1.5 M 16-bit symbols at W = 64 in 367 units 14.7 -> 9.0 us; n = 16,
-// 64 MiB at W = 32 in 256 units 1358 -> 923 us.
+// What bounds it: the chain, about 46 ns per group (mad, compare, count, address, select,
+// 8 cycles each for a lone wave, and an LDS read of 44); without a helper the look-ups come
+// on top, 15 ns per group at 0.36 words per symbol. Measured with the throughput kernel (one
+// wave per workgroup), without a helper and with it: 64 MiB of bytes at W = 32 in 256 units
+// 883, 530, 383 us, in 1024 units 225, 138, 117 us; at W = 64 in 256 units 406, 237, 202 us;
+// 1 MiB at W = 32 in 256 units 18.9, 13.6, 11.9 us; 1.5 M 16-bit symbols at W = 64 in 367
+// units 14.7, 10.8, 10.4 us; n = 16, 64 MiB at W = 32 in 256 units 1358, 930, 676 us.
 #pragma once
 
 #include "decode_core.hpp"
@@ -84,11 +85,16 @@ struct FewTable<Sym, true> {
 
 // K groups per super-step, ring of NCH chunks of C = K*W entries plus a C-entry mirror
 // of its top chunk below slot 0 (as in decode_core.hpp, high to low).
-template <int W, typename Sym, int K, int NCH, bool WIDE, bool COUNT>
+//
+// HELP: a second wave of the workgroup looks the words up and fills the ring (supply()),
+// in step with the decoding one: see super_step.
+template <int W, typename Sym, int K, int NCH, bool WIDE, bool COUNT, bool HELP>
 struct FewDecoder {
     using T = FewTable<Sym, WIDE>;
     static constexpr uint32_t C = K * W, R = NCH * C, E = 8;
     static constexpr uint32_t RING_BYTES = E * (R + C);
+    static constexpr uint32_t MSG = RING_BYTES - E;   // HELP: two words, in place of the mirror's
+                                                      // last entry, which no super-step reaches
     static constexpr uint32_t D = K / 2;      // dwords of a chunk per lane
     static constexpr int32_t FILL = 2;        // chunks looked up before the first group
     static_assert(K % 2 == 0 && NCH >= 3, "ring shape");
@@ -99,11 +105,12 @@ struct FewDecoder {
     bool full;
     uint32_t rec, act, lim, x;
     bool active;
-    uint32_t a;             // LDS address of the unit's next entry
+    uint32_t a, a0;         // LDS address of the unit's next entry, and at the super-step's start
     int32_t res;            // words in the ring: (next word + 1) - fq * C
     int32_t fq;             // lowest chunk in the ring
     bool pend;              // chunk fq - 1 has been requested into pre (there is one)
     uint32_t age;           // super-steps since
+    uint32_t turn;          // HELP: which word of MSG is next, 0 or 4
     uint32_t pre[D];
     uint32_t lane_off;
 
@@ -152,8 +159,15 @@ struct FewDecoder {
             lds_st<u32x4>(at - 2u * E * W * i, u32x4{e[2 * i + 1].x, e[2 * i + 1].y, e[2 * i].x, e[2 * i].y});
         if (pos == NCH - 1) {
 #pragma unroll
-            for (uint32_t i = 0; i < D; ++i)
-                lds_st<u32x4>(at + E * R - 2u * E * W * i, u32x4{e[2 * i + 1].x, e[2 * i + 1].y, e[2 * i].x, e[2 * i].y});
+            for (uint32_t i = 0; i < D; ++i) {
+                const uint32_t to = at + E * R - 2u * E * W * i;
+                if (HELP && i == 0) {
+                    lds_st<u32x2>(to, e[1]);
+                    if (lane != 0) lds_st<u32x2>(to + E, e[0]);   // (lane 0's is MSG)
+                } else {
+                    lds_st<u32x4>(to, u32x4{e[2 * i + 1].x, e[2 * i + 1].y, e[2 * i].x, e[2 * i].y});
+                }
+            }
         }
     }
 
@@ -179,19 +193,63 @@ struct FewDecoder {
         a = uni(slot_addr(cur > 0 ? (cur - 1) % (int32_t)R : 0));
     }
 
-    // First chunks of the run, and the one after them: all requested, then looked up.
-    __device__ __forceinline__ void fill_request(uint32_t (&v)[FILL][D]) {
+    // First chunks of the run, and the one after them: all requested, then looked up. HELP:
+    // the decoding wave takes the highest, its helper the others.
+    __device__ __forceinline__ void fill_request(uint32_t (&v)[FILL][D], bool helper) {
 #pragma unroll
         for (int32_t i = FILL - 1; i >= 0; --i)
-            if (res > i * (int32_t)C) fetch(fq + i, v[i]);
+            if (res > i * (int32_t)C && (!HELP || helper == (i < FILL - 1))) fetch(fq + i, v[i]);
         pend = fq > 0;
         age = 0;
-        if (pend) fetch(fq - 1, pre);
+        if (pend && (!HELP || helper)) fetch(fq - 1, pre);
     }
-    __device__ __forceinline__ void fill_put(const uint32_t (&v)[FILL][D]) {
+    __device__ __forceinline__ void fill_put(const uint32_t (&v)[FILL][D], bool helper) {
 #pragma unroll
         for (int32_t i = FILL - 1; i >= 0; --i)
-            if (res > i * (int32_t)C) put(fq + i, v[i]);
+            if (res > i * (int32_t)C && (!HELP || helper == (i < FILL - 1))) put(fq + i, v[i]);
+        if constexpr (HELP) {
+            turn = 0;
+            meet();
+        }
+    }
+
+    // HELP. The two waves meet once before the first super-step and once after each, where the
+    // decoding wave says how many words are left in the ring. From that number both decide
+    // alike whether the next chunk goes in (claim), and the helper puts it there while the
+    // next super-step runs.
+    //   Supply: more than C words are in the ring at the start of a super-step, or all that
+    // are left, as a super-step takes at most C and a chunk is claimed at up to 2C: before
+    // the first one res > C, and after one that starts with r > 2C still r - C > C, after
+    // one that starts with less r - C + C, the chunk claimed at its start.
+    //   Overwriting: with at most R - C words left, those that the chunk's place held before
+    // have all been read.
+    //   MSG has two words, so that one is not written again before the helper has read it; the
+    // last report ends the helper, so both waves meet the same number of times.
+    static constexpr int32_t kDone = INT32_MIN;
+    __device__ static __forceinline__ void meet() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+    __device__ __forceinline__ void report(int32_t left) {
+        lds_st<uint32_t>(ring + MSG + turn, (uint32_t)left);
+        turn ^= 4u;
+    }
+    __device__ __forceinline__ bool claim() {
+        if (!pend || res > (int32_t)(R - C)) return false;
+        fq -= 1;
+        res += (int32_t)C;
+        pend = fq > 0;
+        return true;
+    }
+    __device__ __forceinline__ void supply() {
+        res = (int32_t)uni((uint32_t)res), fq = (int32_t)uni((uint32_t)fq);
+        for (;;) {
+            if (claim()) {
+                put(fq, pre);
+                if (pend) fetch(fq - 1, pre);
+            }
+            meet();
+            res = (int32_t)uni(lds_ld<uint32_t>(ring + MSG + turn));
+            turn ^= 4u;
+            if (res == kDone) return;
+        }
     }
 
     // Read and decode step of one group for this lane (need: x < L and on), in three parts.
@@ -250,7 +308,9 @@ struct FewDecoder {
         const uint32_t f = factor_of(r), base = T::base(r.need, x, mask);
         advance(r);
         if constexpr (G > 0) emit<G - 1u>(outh, sym);
+        if constexpr (HELP && G == K - 1u) account();
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (HELP && G == K - 1u) meet();
         x = T::next(r.e, f, base);
         sym = T::symbol(r.e);
     }
@@ -292,6 +352,18 @@ struct FewDecoder {
         }
     }
 
+    // The super-step's words, off the ring.
+    __device__ __forceinline__ void consumed() {
+        res -= (int32_t)((a - a0) >> 3);
+        a = a >= slot_addr(-1) ? a - E * R : a;
+    }
+    // HELP: all that the decoding wave does about the ring after a super-step.
+    __device__ __forceinline__ void account() {
+        consumed();
+        report(res);
+        claim();
+    }
+
     static constexpr int kFast = 0, kSync = 1, kPred = 2;
 
     template <int MODE, uint32_t... G>
@@ -317,10 +389,16 @@ struct FewDecoder {
     static constexpr uint32_t AGE = K >= 16 ? 1 : 16 / K;
     template <int MODE, uint32_t KK = K>
     __device__ __forceinline__ bool super_step(uint32_t k) {
-        const uint32_t a0 = a;
+        a0 = a;
         groups<MODE>(std::make_integer_sequence<uint32_t, KK>{}, k);
-        res -= (int32_t)((a - a0) >> 3);
-        a = a >= slot_addr(-1) ? a - E * R : a;
+        if constexpr (HELP) {
+            if constexpr (MODE != kFast) {
+                account();
+                meet();
+            }
+            return res >= 0;
+        }
+        consumed();
         ++age;
         if (pend && (res < (int32_t)C || (res <= (int32_t)(R - C) && age >= AGE))) {
             fq -= 1;
@@ -333,10 +411,19 @@ struct FewDecoder {
         return res >= 0;
     }
 
-    // Decodes the run: the same phases and run-on rule as PairDecoder::run with one unit.
     __device__ __forceinline__ void run() {
+        decode();
+        if constexpr (HELP) {
+            report(kDone);
+            meet();
+        }
+    }
+
+    // Decodes the run: the same phases and run-on rule as PairDecoder::run with one unit.
+    __device__ __forceinline__ void decode() {
         top = uni(top), ghi = uni(ghi), steps = uni(steps), presync = uni(presync);
         a = uni(a), res = (int32_t)uni((uint32_t)res), fq = (int32_t)uni((uint32_t)fq);
+        if constexpr (HELP) claim();
         if (steps == 0) return;
         bool ok = true;
         uint32_t k = 0;

@@ -69,6 +69,26 @@ def test_few_runs_word_rate(rc, W, dt, n, A, M):
 
 
 
+@pytest.mark.parametrize("W,dt,n,A,M,groups", [
+    (32, np.uint8, 11, 256, 300, 150), (64, np.uint8, 12, 256, 800, 130), (32, np.uint16, 12, 4095, 1000, 255),
+    (64, np.uint16, 16, 4096, 900, 90), (64, np.uint8, 12, 256, 500, 300)])
+def test_few_runs_supply(rc, W, dt, n, A, M, groups):
+    """The ring is filled by a second wave, told after each super-step of 4, 8 or 16 groups
+    what is left: runs that read a word in almost every lane of every group, hardly any, and
+    both in turn, next to one another in one launch."""
+    _say("case supply", W, np.dtype(dt).name, n, A, M, groups)
+    f = np.ones(A, dtype=np.uint32)
+    f[0] = (1 << n) - (A - 1)
+    s = _syms(6350, M * groups * W + 5, A, dt).reshape(-1)
+    i = np.arange(s.size) // W
+    s[(i // (3 * groups)) % 3 == 0] = 0                # whole runs without a word
+    s[((i // (3 * groups)) % 3 == 1) & (i // 11 % 2 == 0)] = 0
+    blob = rc.encode(s, lanes=W, quant_bits=n, splits=M, alphabet=A, freq=f)
+    sh = rc.Plan(blob).shape()
+    assert sh.waves_per_block == 1 and sh.runs <= _simds()
+    assert np.array_equal(gpu_decode(rc, blob), s)
+
+
 @pytest.mark.parametrize("W,dt,n,N,M", [
     (32, np.uint8, 12, 3_000_017, 1500), (32, np.uint8, 9, 64 * 2048 * 40, 1025), (64, np.uint16, 12, 3_000_003, 2048),
     (64, np.uint8, 16, 4_000_001, 1100), (32, np.uint8, 11, 1025 * 32 * 300, 1025)])
