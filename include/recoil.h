@@ -116,9 +116,12 @@ typedef struct {
  *                  16, or 1 when the decode has no more wave-sized pieces of work
  *                  (runs, or run pairs for W = 32) than the chip has SIMDs, or 8
  *                  when 16-wave workgroups would not reach every CU, so that the
- *                  waves spread over all CUs
+ *                  waves spread over all CUs. With 0, 1 and 8 a decode of at most
+ *                  two runs per SIMD goes to a kernel of its own (at most one: 1 wave
+ *                  decodes per workgroup; above: 8)
  *   chunk_groups   K (4 or 8): symbol groups per super-step; each unit's LDS bitstream
- *                  ring holds 4 K W words (3 K W ring + K W mirror)
+ *                  ring holds 4 K W words (3 K W ring + K W mirror). The kernel for few
+ *                  runs chooses its own (4, 8 or 16)
  *   pairs_per_wave batched decode only: work-item size in unit pairs per wave (1..64)
  *   blocks_per_cu  cap on resident workgroups per CU (0: occupancy limit)
  *   units_per_run  k consecutive decode units are decoded as one, from the highest

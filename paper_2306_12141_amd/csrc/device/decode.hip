@@ -159,38 +159,7 @@ hipError_t launch_units(const DecodeParams &p, const DecodeTuning &t, hipStream_
 constexpr uint32_t kSimdsPerCu = 4;
 
 template <int W, typename Sym, int VAR>
-hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
-    if (t.waves == 0) {
-        // Automatic: 16 waves per workgroup; one when the launch has no more
-        // wave-sized pieces of work than the chip has SIMDs, and 8 when 16-wave
-        // workgroups would not reach every CU. A 16-wave grid of few pieces puts
-        // four waves on each SIMD of a few CUs and leaves the rest idle, while
-        // each wave's decode is one latency-bound chain that runs faster with
-        // fewer waves beside it. Up to two runs per SIMD the kernel of few.hip
-        // decodes it, whose chain is half as long (its 8-byte table and ring
-        // entries leave no room in the LDS for more).
-        DecodeTuning u = t;
-        u.waves = 16;
-        DecodeShape s{};
-        const hipError_t e = launch_shape<W, Sym, VAR>(p, u, stream, &s);
-        if (e != hipSuccess) return e;
-        const uint64_t pieces = s.units_per_wave ? (s.runs + s.units_per_wave - 1) / s.units_per_wave : 0;
-        const uint64_t cus = (uint64_t)device_cus();
-        if (VAR != kAdaptive && s.units_per_wave == 1) {
-            DecodeParams q = p;
-            q.run = s.units_per_run;
-            q.runs = s.runs;
-            FewShape few{};
-            hipError_t fe = hipSuccess;
-            if (decode_few(q, W, sizeof(Sym), few, shape == nullptr, stream, &fe)) {
-                if (shape) *shape = DecodeShape{few.blocks, few.waves, s.units_per_run, s.runs, 1u};
-                return fe;
-            }
-        }
-        if (pieces <= kSimdsPerCu * cus) u.waves = 1;
-        else if (pieces < 16 * cus) u.waves = 8;
-        return launch_shape<W, Sym, VAR>(p, u, stream, shape);
-    }
+hipError_t launch_fixed(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
     if (t.chunk_groups == 4 && t.waves == 1) return launch_units<W, Sym, 4, 1, VAR>(p, t, stream, shape);
     if (t.chunk_groups == 4 && t.waves == 16) return launch_units<W, Sym, 4, 16, VAR>(p, t, stream, shape);
     if (t.chunk_groups == 4 && t.waves == 8) return launch_units<W, Sym, 4, 8, VAR>(p, t, stream, shape);
@@ -200,6 +169,43 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
         if (t.chunk_groups == 8 && t.waves == 16) return launch_units<W, Sym, 8, 16, VAR>(p, t, stream, shape);
     }
     return hipErrorInvalidValue;
+}
+
+// Automatic (waves = 0): 16 waves per workgroup; one when the launch has no more
+// wave-sized pieces of work than the chip has SIMDs, and 8 when 16-wave workgroups
+// would not reach every CU. A 16-wave grid of few pieces puts four waves on each SIMD
+// of a few CUs and leaves the rest idle, while each wave's decode is one
+// latency-bound chain that runs faster with fewer waves beside it. Up to two runs per
+// SIMD the kernel of few.hip decodes it, whose chain is half as long (its 8-byte table
+// and ring entries leave no room in the LDS for more): also where one or eight waves
+// are asked for and that is the shape it takes, so that a tuned plan is not left with
+// the slower kernel (64 MiB at W = 32 in 256 units, waves = 1: 883 against 383 us).
+template <int W, typename Sym, int VAR>
+hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
+    if (t.waves == 16) return launch_fixed<W, Sym, VAR>(p, t, stream, shape);
+    DecodeTuning u = t;
+    if (t.waves == 0) u.waves = 16;
+    DecodeShape s{};
+    const hipError_t e = launch_fixed<W, Sym, VAR>(p, u, stream, &s);
+    if (e != hipSuccess) return e;
+    if (VAR != kAdaptive && s.units_per_wave == 1 && (t.waves == 0 || t.blocks_per_cu == 0)) {
+        DecodeParams q = p;
+        q.run = s.units_per_run;
+        q.runs = s.runs;
+        FewShape few{};
+        hipError_t fe = hipSuccess;
+        if (decode_few(q, W, sizeof(Sym), t.waves, few, shape == nullptr, stream, &fe)) {
+            if (shape) *shape = DecodeShape{few.blocks, few.waves, s.units_per_run, s.runs, 1u};
+            return fe;
+        }
+    }
+    if (t.waves == 0) {
+        const uint64_t pieces = s.units_per_wave ? (s.runs + s.units_per_wave - 1) / s.units_per_wave : 0;
+        const uint64_t cus = (uint64_t)device_cus();
+        if (pieces <= kSimdsPerCu * cus) u.waves = 1;
+        else if (pieces < 16 * cus) u.waves = 8;
+    }
+    return launch_fixed<W, Sym, VAR>(p, u, stream, shape);
 }
 
 }  // namespace

@@ -58,11 +58,12 @@ struct DecodeParams {
                                 // from its own 32-bit final states, no synchronisation, no run-on
 };
 
-// Launch shape of the single-stream kernel: waves per workgroup (1, 8 or 16;
+// Launch shape of the single-stream kernels: waves per workgroup (1, 8 or 16;
 // 0 = 16, or 1 when the launch has no more waves of work than the chip has
 // SIMDs, or 8 when 16-wave workgroups would not reach every CU), groups per
-// super-step K (4 or 8), workgroups per CU cap (0 =
-// occupancy limit), units per run (0 = chosen from the number of resident waves).
+// super-step K (4 or 8; the kernel for few runs takes its own), workgroups per CU
+// cap (0 = occupancy limit), units per run (0 = chosen from the number of resident
+// waves).
 struct DecodeTuning {
     uint32_t waves = 0, chunk_groups = 4, blocks_per_cu = 0, units_per_run = 0;
 };

@@ -145,3 +145,32 @@ def test_adaptive_index_blocks(rc, W, N, M):
             plan.decode_adaptive(ws, index, out, err)
             torch.cuda.synchronize()
             assert int(err.item()) == 0 and np.array_equal(plan.symbols_of(out), s)
+
+
+@pytest.mark.parametrize("W,dt,n,M", [(32, np.uint8, 11, 300), (64, np.uint16, 12, 1500), (64, np.uint8, 16, 1100)])
+def test_tuned_waves(rc, W, dt, n, M):
+    """One or eight waves asked for: the kernel for few runs where that is its shape, the
+    throughput kernel otherwise and under a cap on resident workgroups; 16 keeps the latter."""
+    _say("case tuned waves", W, np.dtype(dt).name, n, M)
+    A = 256 if dt == np.uint8 else 4096
+    s = _syms(6700 + M, 2_000_011, A, dt, 1.1)
+    blob = rc.encode(s, lanes=W, quant_bits=n, splits=M, alphabet=A)
+    cus = _simds() // 4
+    for waves in (1, 8, 16):
+        for cap in (0, 1):
+            for k in (4, 8):
+                plan = rc.Plan(blob)
+                plan.set_tuning(waves, k, cap, 1)
+                sh = plan.shape()
+                assert sh.runs == blob.splits and sh.waves_per_block == waves
+                if waves == 8 and cap == 0 and blob.splits > 4 * cus:
+                    assert sh.blocks == cus
+                ws = plan.allocate_workspace()
+                plan.upload(ws)
+                out = plan.allocate_output()
+                out.fill_(0x5A)
+                err = torch.zeros(1, dtype=torch.int32, device="cuda")
+                plan.decode(ws, out, err)
+                torch.cuda.synchronize()
+                assert int(err.item()) == 0
+                assert np.array_equal(plan.symbols_of(out), s)
