@@ -1,8 +1,7 @@
 // Decode launches of few runs (see few_core.hpp). Up to one run per SIMD: a workgroup per
 // run, decoded by its first wave and supplied with looked-up words by its second; all but
 // the first stage the decode table, while the first one fetches its records and its first
-// words. Up to two per SIMD: a workgroup per CU, whose waves share one table and look their
-// words up themselves (s_barrier, by which a run's two waves meet, is the whole workgroup's).
+// words. Up to two per SIMD: a workgroup per CU, whose waves share one table.
 //
 // The decoding wave has the higher priority: with four runs on a CU its SIMD also runs
 // another run's helper, which has time (n = 16, 64 MiB at W = 32 in 1024 units: 189 us
@@ -27,10 +26,18 @@ constexpr uint32_t kLdsBytes = 160u << 10;   // per CU
 constexpr uint32_t kLongRun = 256;
 constexpr int kRing = 3;                     // chunks of a ring
 
-// Decoding waves of a workgroup, and its threads.
+// Decoding waves of a workgroup, whether each has a helper, and its threads. In shared
+// workgroups the waves of all runs meet at once, the helpers of 32-lane runs keep half
+// their lanes idle and those of wide tables take two reads per word, so that only 64-lane
+// runs on one-level tables gain (without and with helpers, 64 MiB of bytes or 32 Mi 16-bit
+// symbols: W = 64, 2048 units 58.6 and 55.3 us, 16-bit 37.4 and 36.4 us, n = 16 80.4 and
+// 83.2 us, 1100 units 87.4 and 78.6 us; W = 32, 2048 units 81.5 and 86.5 us, n = 16 131.5
+// and 134.6 us).
 constexpr int kShared = 8;
-template <int WAVES>
-constexpr uint32_t kThreads = WAVES == 1 ? 256 : 64 * WAVES;
+template <int W, bool WIDE, int WAVES>
+constexpr bool kHelp = WAVES == 1 || (W == 64 && !WIDE);
+template <int W, bool WIDE, int WAVES>
+constexpr uint32_t kThreads = WAVES == 1 ? 256 : 64 * WAVES * (kHelp<W, WIDE, WAVES> ? 2 : 1);
 
 template <typename Sym, bool WIDE>
 __device__ inline void stage_table(const DecodeParams &p, uint32_t lut, uint32_t tid, uint32_t threads) {
@@ -57,14 +64,14 @@ __host__ __device__ inline uint32_t table_bytes(uint32_t lut_bytes) {
 }
 
 template <int W, typename Sym, int K, bool WIDE, bool COUNT, int WAVES>
-__global__ __launch_bounds__(kThreads<WAVES>) void decode_few_runs(DecodeParams p) {
-    constexpr bool HELP = WAVES == 1;
+__global__ __launch_bounds__((kThreads<W, WIDE, WAVES>)) void decode_few_runs(DecodeParams p) {
+    constexpr bool HELP = kHelp<W, WIDE, WAVES>;
     using D = FewDecoder<W, Sym, K, kRing, WIDE, COUNT, HELP>;
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t lut = lds_addr(smem);
     const uint32_t wave = uni(threadIdx.x >> 6);
-    const bool helps = HELP && wave == WAVES;
-    const uint32_t slot = helps ? 0u : wave;
+    const bool helps = HELP && wave >= WAVES;
+    const uint32_t slot = helps ? wave - WAVES : wave;
     const uint32_t run = blockIdx.x + slot * gridDim.x;
     const bool works = slot < WAVES && run < p.runs;
     D d(p, lut, lut + table_bytes<Sym, WIDE>(p.lut_bytes) + slot * D::RING_BYTES, threadIdx.x & (W - 1u));
@@ -73,8 +80,8 @@ __global__ __launch_bounds__(kThreads<WAVES>) void decode_few_runs(DecodeParams 
         d.records(run);
         d.fill_request(v, helps);
     }
-    if (WAVES > 1) stage_table<Sym, WIDE>(p, lut, threadIdx.x, kThreads<WAVES>);
-    else if (wave > 0) stage_table<Sym, WIDE>(p, lut, threadIdx.x - 64, kThreads<WAVES> - 64);
+    if (WAVES > 1) stage_table<Sym, WIDE>(p, lut, threadIdx.x, kThreads<W, WIDE, WAVES>);
+    else if (wave > 0) stage_table<Sym, WIDE>(p, lut, threadIdx.x - 64, kThreads<W, WIDE, WAVES> - 64);
     __syncthreads();
     if (!works) return;     // (s_barrier does not wait for waves that have ended)
     if (W < 64 && (threadIdx.x & 63u) >= W) return;     // lanes without a coder
@@ -89,11 +96,11 @@ __global__ __launch_bounds__(kThreads<WAVES>) void decode_few_runs(DecodeParams 
 
 template <int W, typename Sym, int K, bool WIDE, bool COUNT, int WAVES>
 bool try_launch(const DecodeParams &p, const FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
-    const uint32_t lds = table_bytes<Sym, WIDE>(p.lut_bytes) + WAVES * FewDecoder<W, Sym, K, kRing, WIDE, COUNT, WAVES == 1>::RING_BYTES;
+    const uint32_t lds = table_bytes<Sym, WIDE>(p.lut_bytes) + WAVES * FewDecoder<W, Sym, K, kRing, WIDE, COUNT, kHelp<W, WIDE, WAVES>>::RING_BYTES;
     const uint32_t cus = (uint32_t)device_cus(), per_cu = (shape.blocks + cus - 1) / cus;
     if (lds * per_cu > kLdsBytes) return false;
     if (launch) {
-        hipLaunchKernelGGL((decode_few_runs<W, Sym, K, WIDE, COUNT, WAVES>), dim3(shape.blocks), dim3(kThreads<WAVES>), lds,
+        hipLaunchKernelGGL((decode_few_runs<W, Sym, K, WIDE, COUNT, WAVES>), dim3(shape.blocks), dim3((kThreads<W, WIDE, WAVES>)), lds,
                            stream, p);
         *e = hipGetLastError();
     }
