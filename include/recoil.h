@@ -123,7 +123,9 @@ typedef struct {
  *                  ring holds 4 K W words (3 K W ring + K W mirror). The kernel for few
  *                  runs chooses its own (4, 8 or 16)
  *   pairs_per_wave batched decode only: work-item size in unit pairs per wave (1..64)
- *   blocks_per_cu  cap on resident workgroups per CU (0: occupancy limit)
+ *   blocks_per_cu  cap on resident workgroups per CU (0: occupancy limit). The kernel for
+ *                  few runs keeps one workgroup per run (above one run per SIMD: per CU)
+ *                  resident and is not used where that exceeds the cap
  *   units_per_run  k consecutive decode units are decoded as one, from the highest
  *                  unit's split point down to the lowest unit's last group (the decoder
  *                  uses every k-th split point, as combining the splits would, Sec. 3.3,

@@ -179,7 +179,9 @@ hipError_t launch_fixed(const DecodeParams &p, const DecodeTuning &t, hipStream_
 // SIMD the kernel of few.hip decodes it, whose chain is half as long (its 8-byte table
 // and ring entries leave no room in the LDS for more): also where one or eight waves
 // are asked for and that is the shape it takes, so that a tuned plan is not left with
-// the slower kernel (64 MiB at W = 32 in 256 units, waves = 1: 883 against 383 us).
+// the slower kernel (64 MiB at W = 32 in 256 units, waves = 1: 883 against 383 us). A cap on
+// the resident workgroups keeps the throughput kernel where waves are asked for, and where
+// they are not if the few-run kernel's grid would exceed it.
 template <int W, typename Sym, int VAR>
 hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
     if (t.waves == 16) return launch_fixed<W, Sym, VAR>(p, t, stream, shape);
@@ -194,7 +196,7 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
         q.runs = s.runs;
         FewShape few{};
         hipError_t fe = hipSuccess;
-        if (decode_few(q, W, sizeof(Sym), t.waves, few, shape == nullptr, stream, &fe)) {
+        if (decode_few(q, W, sizeof(Sym), t.waves, t.blocks_per_cu, few, shape == nullptr, stream, &fe)) {
             if (shape) *shape = DecodeShape{few.blocks, few.waves, s.units_per_run, s.runs, 1u};
             return fe;
         }

@@ -133,8 +133,8 @@ bool pick_variant(const DecodeParams &p, const FewShape &shape, bool launch, hip
 
 }  // namespace
 
-bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, uint32_t waves, FewShape &shape,
-                bool launch, hipStream_t stream, hipError_t *e) {
+bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, uint32_t waves, uint32_t blocks_per_cu,
+                FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
     constexpr uint32_t kSimds = 4;   // per CU
     const uint32_t cus = (uint32_t)device_cus();
     // Two runs per SIMD still run at almost the pace of one (64 MiB at W = 32 in 2048 units:
@@ -143,6 +143,9 @@ bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, ui
     if (p.tidx || p.runs == 0 || p.runs > 2 * kSimds * cus) return false;
     shape = p.runs <= kSimds * cus ? FewShape{p.runs, 1} : FewShape{cus, (uint32_t)kShared};
     if (waves && waves != shape.waves) return false;
+    // Every run is resident from the start, so a cap below that is left to the throughput
+    // kernel, whose workgroups decode one run after another.
+    if (blocks_per_cu && (shape.blocks + cus - 1) / cus > blocks_per_cu) return false;
     static_assert(kShared == 2 * kSimds, "a workgroup per CU holds two runs per SIMD");
     if (lanes == 32) return symbol_bytes == 1 ? pick_variant<32, uint8_t>(p, shape, launch, stream, e)
                                               : pick_variant<32, uint16_t>(p, shape, launch, stream, e);
