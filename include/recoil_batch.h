@@ -28,21 +28,24 @@ recoil_tuning recoil_default_tuning(void);
  * queue counter) and the output size: stream i's symbols land at the offset given
  * by recoil_batch_output_offset (256-byte aligned). tuning: NULL for the default.
  * Streams with 13 <= n <= 16 (two-level tables) form a table class decoded by a
- * launch of its own. Errors: INVALID_ARG, UNSUPPORTED (see recoil_plan_create; also
- * adaptive streams, which are decoded alone).
+ * launch of its own. Host work only, no HIP call: the work items, which depend on the
+ * device, are built by the first call that needs them, for the device current then.
+ * Errors: INVALID_ARG, UNSUPPORTED (see recoil_plan_create; also adaptive streams, which
+ * are decoded alone).
  */
 recoil_status recoil_batch_create(const recoil_blob *const *blobs, uint32_t count, const recoil_tuning *tuning,
                                   recoil_batch **out, size_t *workspace_bytes, size_t *output_bytes);
 void recoil_batch_free(recoil_batch *batch);
 recoil_status recoil_batch_output_offset(const recoil_batch *batch, uint32_t index, uint64_t *offset, uint64_t *bytes);
-uint32_t recoil_batch_items(const recoil_batch *batch);
+uint32_t recoil_batch_items(const recoil_batch *batch);   /* work items; 0 if they cannot be built */
 
 /* Asynchronous H2D copy of everything into d_workspace (256-byte aligned).
  * Errors: INVALID_ARG, BUFFER_TOO_SMALL, ALIGNMENT, HIP. */
 recoil_status recoil_batch_upload(const recoil_batch *batch, void *d_workspace, size_t bytes, hipStream_t stream);
 
-/* Change the launch shape; rebuilds the work items on the host and, if
- * d_workspace is not NULL, re-uploads them on `stream`. Errors: INVALID_ARG, HIP. */
+/* Change the launch shape. If d_workspace is not NULL, rebuilds the work items and
+ * re-uploads them on `stream`; otherwise (no HIP call) the next upload brings them.
+ * Not while another call uses the batch. Errors: INVALID_ARG, HIP. */
 recoil_status recoil_batch_set_tuning(recoil_batch *batch, const recoil_tuning *tuning, void *d_workspace,
                                       hipStream_t stream);
 recoil_status recoil_batch_get_tuning(const recoil_batch *batch, recoil_tuning *tuning);

@@ -2,6 +2,7 @@
 // layout, the persistent launch, the one-launch-per-stream baseline, HIP graph
 // capture and the autotuner.
 #include <algorithm>
+#include <atomic>
 #include <memory>
 #include <chrono>
 #include <cstring>
@@ -62,6 +63,8 @@ struct BatchShape {
     bool single = false;     // every W = 32 unit on a wave of its own
 };
 
+constexpr uint64_t kMaxCus = 256, kWavesPerCu = 32;   // gfx950; a partition has fewer CUs
+
 // units_per_run = 0 leaves the shape to the batch's size; otherwise it is the tuning's.
 //
 // Every split point is used. Items are waves x pairs_per_wave pairs, or fewer, so that a
@@ -78,8 +81,7 @@ BatchShape batch_shape(const BatchData &b) {
     sh.per_item = std::max(1u, t.waves * t.pairs_per_wave);
     sh.run = std::max(1u, t.units_per_run);
     if (t.units_per_run != 0) return sh;
-    const uint64_t cus = device_cus() > 1 ? (uint64_t)device_cus() : 256u;
-    constexpr uint64_t kWavesPerCu = 32;
+    const uint64_t cus = device_cus() > 1 ? std::min((uint64_t)device_cus(), kMaxCus) : kMaxCus;
     std::vector<uint32_t> units, pairs;   // of each stream, every split point used
     uint64_t all_units = 0, all_pairs = 0;
     for (const PlanData &pl : b.plans) {
@@ -155,6 +157,22 @@ void build_items(BatchData &b) {
     }
 }
 
+// Items that any tuning gives at most: the workspace's size depends on neither the tuning nor
+// the device. An item of the tuning's own size has waves x pairs_per_wave >= 8 pairs or single
+// units, or a stream's last ones; smaller items are cut only as long as a launch has no more
+// of them than the chip holds workgroups (of 8 waves at least), and hold a unit each.
+size_t items_bound(const BatchData &b) {
+    size_t full[kBatchClasses] = {}, units[kBatchClasses] = {}, bound = 0;
+    for (const PlanData &pl : b.plans) {
+        const uint32_t c = table_class(pl), M = pl.single_symbol ? 1 : pl.blob->splits();
+        full[c] += (M + 7) / 8;
+        units[c] += M;
+    }
+    for (uint32_t c = 0; c < kBatchClasses; ++c)
+        bound += std::min<size_t>(units[c], full[c] + kMaxCus * kWavesPerCu / 8);
+    return std::max<size_t>(bound, 1);
+}
+
 bool tuning_ok(const recoil_tuning &t) {
     return (t.waves == 8 || t.waves == 16) && (t.chunk_groups == 4 || t.chunk_groups == 8) && t.pairs_per_wave >= 1 &&
            t.pairs_per_wave <= 64 && t.units_per_run <= 64;
@@ -213,8 +231,28 @@ std::map<std::string, recoil_tuning> g_tune_cache;
 }  // namespace recoil
 
 struct recoil_batch {
-    recoil::BatchData d;
+    mutable recoil::BatchData d;
+    mutable std::mutex mu;
+    mutable std::atomic<bool> items_built{false};
 };
+
+namespace {
+
+// The batch with its work items. They depend on the device (how many workgroups it holds),
+// so they are built for the first call that needs them and not at creation, which is host
+// work alone: a program may create batches before it forks or chooses its device.
+recoil::BatchData &with_items(const recoil_batch *batch) {
+    if (!batch->items_built.load(std::memory_order_acquire)) {
+        std::lock_guard<std::mutex> lk(batch->mu);
+        if (!batch->items_built.load(std::memory_order_relaxed)) {
+            recoil::build_items(batch->d);
+            batch->items_built.store(true, std::memory_order_release);
+        }
+    }
+    return batch->d;
+}
+
+}  // namespace
 
 struct recoil_graph {
     hipGraph_t graph = nullptr;
@@ -244,18 +282,7 @@ recoil_status recoil_batch_create(const recoil_blob *const *blobs, uint32_t coun
         if (st) { return st; }
         b.lut_bytes = std::max<uint32_t>(b.lut_bytes, (uint32_t)b.plans[i].lut.size());
     }
-    // Item capacity: the finest tuning (8 waves, one pair per wave).
-    size_t cap = 0;
-    for (const PlanData &pl : b.plans) cap += pl.single_symbol ? 1 : (pairs_of(pl, 1) + 7) / 8;
-    // A shape left to the batch's size may be finer still.
-    const recoil_tuning asked = b.tuning;
-    for (uint32_t waves : {8u, 16u}) {
-        b.tuning = recoil_tuning{waves, asked.chunk_groups, 1, 0, 0};
-        build_items(b);
-        cap = std::max(cap, b.items.size());
-    }
-    b.tuning = asked;
-    b.items_cap = std::max<size_t>(cap, 1);
+    b.items_cap = items_bound(b);
     size_t off = 0;
     b.off_head = off;  off = ws_align(off + kBatchHeadBytes);
     b.off_descs = off; off = ws_align(off + count * sizeof(StreamDesc));
@@ -289,8 +316,6 @@ recoil_status recoil_batch_create(const recoil_blob *const *blobs, uint32_t coun
     }
     b.total_ws = off;
     b.total_out = std::max<size_t>(out_off, 256);
-    build_items(b);
-    if (b.items.size() > b.items_cap) { return fail(RECOIL_ERR_INVALID_ARG, "batch_create: too many items"); }
     if (workspace_bytes) *workspace_bytes = b.total_ws;
     if (output_bytes) *output_bytes = b.total_out;
     *out = hp.release();
@@ -308,7 +333,15 @@ recoil_status recoil_batch_output_offset(const recoil_batch *batch, uint32_t ind
     return RECOIL_OK;
 }
 
-uint32_t recoil_batch_items(const recoil_batch *batch) { return batch ? (uint32_t)batch->d.items.size() : 0; }
+uint32_t recoil_batch_items(const recoil_batch *batch) {
+    uint32_t items = 0;
+    if (batch)
+        (void)recoil::guarded("batch_items", [&]() -> recoil_status {
+            items = (uint32_t)with_items(batch).items.size();
+            return RECOIL_OK;
+        });
+    return items;
+}
 
 static recoil_status upload_items(const recoil::BatchData &b, void *d_ws, hipStream_t stream) {
     using namespace recoil;
@@ -324,7 +357,7 @@ recoil_status recoil_batch_upload(const recoil_batch *batch, void *d_ws, size_t 
     return recoil::guarded("batch_upload", [&]() -> recoil_status {
     using namespace recoil;
     if (!batch || !d_ws) return fail(RECOIL_ERR_INVALID_ARG, "batch_upload: bad arguments");
-    const BatchData &b = batch->d;
+    const BatchData &b = with_items(batch);
     if (bytes < b.total_ws) return fail(RECOIL_ERR_BUFFER_TOO_SMALL, "batch_upload: workspace too small");
     if (reinterpret_cast<uintptr_t>(d_ws) % kWsAlign) return fail(RECOIL_ERR_ALIGNMENT, "batch_upload: workspace not 256-byte aligned");
     char *base = static_cast<char *>(d_ws);
@@ -350,19 +383,14 @@ recoil_status recoil_batch_upload(const recoil_batch *batch, void *d_ws, size_t 
 }
 
 recoil_status recoil_batch_set_tuning(recoil_batch *batch, const recoil_tuning *t, void *d_ws, hipStream_t stream) {
+    return recoil::guarded("batch_set_tuning", [&]() -> recoil_status {
     using namespace recoil;
     if (!batch || !t || !tuning_ok(*t)) return fail(RECOIL_ERR_INVALID_ARG, "batch_set_tuning: unsupported tuning");
-    const recoil_tuning old = batch->d.tuning;
     batch->d.tuning = *t;
-    build_items(batch->d);
-    if (batch->d.items.size() > batch->d.items_cap) {
-        // Keep the batch as it was: its workspace holds items_cap items.
-        batch->d.tuning = old;
-        build_items(batch->d);
-        return fail(RECOIL_ERR_INVALID_ARG, "batch_set_tuning: too many items");
-    }
-    if (d_ws) return upload_items(batch->d, d_ws, stream);
+    batch->items_built.store(false, std::memory_order_relaxed);   // (of a batch that no other call is using)
+    if (d_ws) return upload_items(with_items(batch), d_ws, stream);
     return RECOIL_OK;
+    });
 }
 
 recoil_status recoil_batch_get_tuning(const recoil_batch *batch, recoil_tuning *t) {
@@ -373,19 +401,22 @@ recoil_status recoil_batch_get_tuning(const recoil_batch *batch, recoil_tuning *
 }
 
 recoil_status recoil_decode_batch(const recoil_batch *batch, void *d_ws, void *d_out, uint32_t *d_error, hipStream_t stream) {
+    return recoil::guarded("decode_batch", [&]() -> recoil_status {
     using namespace recoil;
     if (!batch || !d_ws || !d_out || !d_error) return fail(RECOIL_ERR_INVALID_ARG, "decode_batch: bad arguments");
-    const BatchData &b = batch->d;
+    const BatchData &b = with_items(batch);
     hipError_t e = launch_classes(b, d_ws, d_out, d_error, nullptr, stream);
     if (e != hipSuccess) return fail(RECOIL_ERR_HIP, std::string("decode_batch: ") + hipGetErrorString(e));
     return RECOIL_OK;
+    });
 }
 
 recoil_status recoil_decode_batch_noalloc(const recoil_batch *batch, const void *d_ws, void *d_out, uint32_t *d_error,
                                          hipStream_t stream) {
+    return recoil::guarded("decode_batch_noalloc", [&]() -> recoil_status {
     using namespace recoil;
     if (!batch || !d_ws || !d_out || !d_error) return fail(RECOIL_ERR_INVALID_ARG, "decode_batch_noalloc: bad arguments");
-    const BatchData &b = batch->d;
+    const BatchData &b = with_items(batch);
     // One queue head per table class in the library's static device array.
     static_assert(kBatchClasses * kStaticHeadStride <= kStaticScratchWords, "static queue heads do not fit");
     uint32_t classes = 0;
@@ -400,6 +431,7 @@ recoil_status recoil_decode_batch_noalloc(const recoil_batch *batch, const void 
     e = launch_classes(b, const_cast<void *>(d_ws), d_out, d_error, reinterpret_cast<unsigned char *>(heads), stream);
     if (e != hipSuccess) return fail(RECOIL_ERR_HIP, std::string("decode_batch_noalloc: ") + hipGetErrorString(e));
     return RECOIL_OK;
+    });
 }
 
 recoil_status recoil_decode_batch_per_stream(const recoil_batch *batch, const void *d_ws, void *d_out,
@@ -437,16 +469,17 @@ recoil_status recoil_decode_batch_per_stream(const recoil_batch *batch, const vo
 
 recoil_status recoil_batch_graph_create(const recoil_batch *batch, void *d_ws, void *d_out, uint32_t *d_error,
                                         recoil_graph **out) {
+    return recoil::guarded("batch_graph_create", [&]() -> recoil_status {
     using namespace recoil;
     if (!batch || !out) return fail(RECOIL_ERR_INVALID_ARG, "batch_graph_create: bad arguments");
     *out = nullptr;
+    const BatchData &b = with_items(batch);
     auto *g = new (std::nothrow) recoil_graph();
     if (!g) return fail(RECOIL_ERR_INVALID_ARG, "batch_graph_create: out of memory");
     hipStream_t cs = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        const BatchData &b = batch->d;
         hipError_t le = launch_classes(b, d_ws, d_out, d_error, nullptr, cs);
         e = hipStreamEndCapture(cs, &g->graph);
         if (le != hipSuccess) e = le;
@@ -461,6 +494,7 @@ recoil_status recoil_batch_graph_create(const recoil_batch *batch, void *d_ws, v
     }
     *out = g;
     return RECOIL_OK;
+    });
 }
 
 recoil_status recoil_graph_launch(recoil_graph *g, hipStream_t stream) {
@@ -480,9 +514,10 @@ void recoil_graph_free(recoil_graph *g) {
 
 recoil_status recoil_autotune(recoil_batch *batch, void *d_ws, void *d_out, uint32_t *d_error, hipStream_t stream,
                               uint32_t reps, recoil_tuning *best_out, float *best_ms) {
+    return recoil::guarded("autotune", [&]() -> recoil_status {
     using namespace recoil;
     if (!batch || !d_ws || !d_out || !d_error || reps == 0) return fail(RECOIL_ERR_INVALID_ARG, "autotune: bad arguments");
-    BatchData &b = batch->d;
+    const BatchData &b = with_items(batch);
     // Cache key: device architecture plus the batch's shape.
     hipDeviceProp_t prop{};
     int dev = 0;
@@ -549,6 +584,7 @@ recoil_status recoil_autotune(recoil_batch *batch, void *d_ws, void *d_out, uint
     if (best_out) *best_out = best;
     if (best_ms) *best_ms = best_t;
     return RECOIL_OK;
+    });
 }
 
 }  // extern "C"
