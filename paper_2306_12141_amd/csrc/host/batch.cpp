@@ -56,7 +56,17 @@ uint32_t pairs_of(const PlanData &pl, uint32_t k) {
     return W == 32 ? (runs + 1) / 2 : runs;
 }
 
-// What the launch does with a batch as a whole.
+BatchTuning device_tuning(const recoil_tuning &t) { return BatchTuning{t.waves, t.chunk_groups, t.blocks_per_cu}; }
+
+// Classes 0 and 1 go into one launch if the larger tables leave as many workgroups per CU
+// (4-group rings do): the classes' last items then overlap.
+bool joined(const BatchData &b) {
+    const BatchTuning t = device_tuning(b.tuning);
+    return b.cls_lut[0] && b.cls_lut[1] &&
+           batch_blocks_per_cu(t, std::max(b.cls_lut[0], b.cls_lut[1])) == batch_blocks_per_cu(t, b.cls_lut[0]);
+}
+
+// What a launch does with its streams as a whole.
 struct BatchShape {
     uint32_t run = 1;        // units per run, before a stream's own limits (units_per_run; 0: 1)
     uint32_t per_item = 1;   // pairs of a work item
@@ -65,35 +75,45 @@ struct BatchShape {
 
 constexpr uint64_t kMaxCus = 256, kWavesPerCu = 32;   // gfx950; a partition has fewer CUs
 
-// units_per_run = 0 leaves the shape to the batch's size; otherwise it is the tuning's.
+// Shape of the launch that decodes classes c0 .. c1. units_per_run = 0 leaves it to the size
+// of their streams; otherwise it is the tuning's.
 //
-// Every split point is used. Items are waves x pairs_per_wave pairs, or fewer, so that a
-// batch of less work than that is spread over all workgroups that the chip holds instead of
-// a few full ones, each item on a workgroup of its own: 60 streams of 4 KiB .. 16 MiB, two
-// launches of 173 and 66 items of 32 pairs 191 us, one of 495 items of 13 pairs 99 us; 24
-// streams up to 1 MiB 56 and 17 us, 40 up to 4 MiB 302 and 109. (300 streams, 105 pairs for
-// each workgroup: items of 16 or 32 pairs 348 and 353 us, runs of two units 358 and 375.)
+// Every split point is used. Items are waves x pairs_per_wave pairs, or fewer, so that
+// streams of less work than that are spread over all workgroups that the chip holds of this
+// launch (its tables and rings may leave room for one per CU) instead of a few full ones, each
+// item on a workgroup of its own: 60 streams of 4 KiB .. 16 MiB, two launches of 173 and 66
+// items of 32 pairs 191 us, one of 495 items of 13 pairs 99 us; 24 streams up to 1 MiB 56 and
+// 17 us, 40 up to 4 MiB 302 and 109. (300 streams, 105 pairs for each workgroup: items of 16
+// or 32 pairs 348 and 353 us, runs of two units 358 and 375.)
+// Cut for two workgroups per CU where the launch holds one, the items go through the queue in
+// two uneven rounds: 24 streams up to 1 MiB at n = 16 in 308 items 64.3 us, in 211 items 38.4;
+// 24 of 16-bit symbols with 8-group rings 48.5 and 27.1; 40 up to 4 MiB capped at one 102.8
+// and 67.6.
 // W = 32 units are decoded one per wave while that takes at most half of the wave slots, as
 // for one stream.
-BatchShape batch_shape(const BatchData &b) {
+BatchShape batch_shape(const BatchData &b, uint32_t c0, uint32_t c1) {
     const recoil_tuning &t = b.tuning;
     BatchShape sh;
     sh.per_item = std::max(1u, t.waves * t.pairs_per_wave);
     sh.run = std::max(1u, t.units_per_run);
     if (t.units_per_run != 0) return sh;
     const uint64_t cus = device_cus() > 1 ? std::min((uint64_t)device_cus(), kMaxCus) : kMaxCus;
+    const int fit = batch_blocks_per_cu(device_tuning(t), std::max(b.cls_lut[c0], b.cls_lut[c1]), c0 == kWideClass);
+    uint64_t per_cu = fit > 0 ? (uint64_t)fit : kWavesPerCu / t.waves;   // (no device: as if only the waves counted)
+    if (t.blocks_per_cu) per_cu = std::min<uint64_t>(per_cu, t.blocks_per_cu);
+    const uint64_t workgroups = cus * per_cu;
     std::vector<uint32_t> units, pairs;   // of each stream, every split point used
     uint64_t all_units = 0, all_pairs = 0;
     for (const PlanData &pl : b.plans) {
-        if (pl.single_symbol || pl.blob->n_symbols == 0) continue;
+        const uint32_t c = table_class(pl);
+        if (c < c0 || c > c1 || pl.single_symbol || pl.blob->n_symbols == 0) continue;
         const uint32_t M = pl.blob->splits();
         units.push_back(M);
         pairs.push_back(M <= t.waves ? M : pairs_of(pl, 1));   // (few units: one per wave, see build_items)
         all_units += M;
         all_pairs += pairs.back();
     }
-    const uint64_t slots = cus * kWavesPerCu, workgroups = std::max<uint64_t>(1, slots / t.waves);
-    sh.single = all_units <= slots / 2;
+    sh.single = all_units <= std::min(workgroups * t.waves, cus * kWavesPerCu / 2);
     const std::vector<uint32_t> &work = sh.single ? units : pairs;
     const uint64_t total = sh.single ? all_units : all_pairs;
     if (total > workgroups * sh.per_item) return sh;
@@ -131,14 +151,24 @@ void build_items(BatchData &b) {
         return b.plans[a].blob->n_symbols * b.plans[a].blob->symbol_bytes >
                b.plans[c].blob->n_symbols * b.plans[c].blob->symbol_bytes;
     });
-    const BatchShape sh = batch_shape(b);
     for (uint32_t c = 0; c < kBatchClasses; ++c) { b.cls_begin[c] = 0; b.cls_count[c] = 0; b.cls_lut[c] = 0; }
+    for (const PlanData &pl : b.plans) {
+        uint32_t &lut = b.cls_lut[table_class(pl)];
+        if (pl.blob->n_symbols) lut = std::max<uint32_t>(lut, (uint32_t)pl.lut.size());
+    }
+    BatchShape shapes[kBatchClasses];
+    for (uint32_t c = 0; c < kBatchClasses; ++c) {
+        if (!b.cls_lut[c]) continue;
+        const bool both = c == 0 && joined(b);
+        shapes[c] = batch_shape(b, c, both ? 1 : c);
+        if (both) { shapes[1] = shapes[0]; ++c; }
+    }
     for (uint32_t s : order) {
         const PlanData &pl = b.plans[s];
         if (pl.blob->n_symbols == 0) continue;
         const uint32_t c = table_class(pl);
+        const BatchShape &sh = shapes[c];
         if (b.cls_count[c] == 0) b.cls_begin[c] = (uint32_t)b.items.size();
-        b.cls_lut[c] = std::max<uint32_t>(b.cls_lut[c], (uint32_t)pl.lut.size());
         const size_t before = b.items.size();
         if (pl.single_symbol) {
             b.items.push_back({s, 0, 1, 1});
@@ -178,10 +208,8 @@ bool tuning_ok(const recoil_tuning &t) {
            t.pairs_per_wave <= 64 && t.units_per_run <= 64;
 }
 
-BatchTuning device_tuning(const recoil_tuning &t) { return BatchTuning{t.waves, t.chunk_groups, t.blocks_per_cu}; }
-
-// A launch: the items of class cls, and with joined set those of the next class too.
-BatchParams params_of(const BatchData &b, uint32_t cls, bool joined, void *d_ws, void *d_out, uint32_t *d_err) {
+// A launch: the items of class cls, and with both set those of the next class too.
+BatchParams params_of(const BatchData &b, uint32_t cls, bool both, void *d_ws, void *d_out, uint32_t *d_err) {
     BatchParams bp{};
     unsigned char *ws = static_cast<unsigned char *>(d_ws);
     bp.ws = ws;
@@ -190,28 +218,25 @@ BatchParams params_of(const BatchData &b, uint32_t cls, bool joined, void *d_ws,
     bp.items = reinterpret_cast<const WorkItem *>(ws + b.off_items) + b.cls_begin[cls];
     bp.head = reinterpret_cast<uint32_t *>(ws + b.off_head + cls * kHeadStride);
     bp.err = d_err;
-    bp.n_items = b.cls_count[cls] + (joined ? b.cls_count[cls + 1] : 0u);
-    bp.lut_bytes = joined ? std::max(b.cls_lut[cls], b.cls_lut[cls + 1]) : b.cls_lut[cls];
+    bp.n_items = b.cls_count[cls] + (both ? b.cls_count[cls + 1] : 0u);
+    bp.lut_bytes = both ? std::max(b.cls_lut[cls], b.cls_lut[cls + 1]) : b.cls_lut[cls];
     bp.wide = cls == kWideClass ? 1u : 0u;
     return bp;
 }
 
-// One persistent launch per table class that has work, in class order; classes 0 and 1
-// in one if the larger tables leave as many workgroups per CU (4-group rings do): the
-// classes' last items then overlap. heads: queue heads kHeadStride bytes apart (NULL: the
-// workspace's).
+// One persistent launch per table class that has work, in class order, or for two (see
+// joined). heads: queue heads kHeadStride bytes apart (NULL: the workspace's).
 hipError_t launch_classes(const BatchData &b, void *d_ws, void *d_out, uint32_t *d_err, unsigned char *heads,
                           hipStream_t stream) {
     const BatchTuning t = device_tuning(b.tuning);
     for (uint32_t c = 0; c < kBatchClasses; ++c) {
         if (b.cls_count[c] == 0) continue;
-        const bool joined = c == 0 && b.cls_count[1] != 0 &&
-                            batch_blocks_per_cu(t, std::max(b.cls_lut[0], b.cls_lut[1])) == batch_blocks_per_cu(t, b.cls_lut[0]);
-        BatchParams bp = params_of(b, c, joined, d_ws, d_out, d_err);
+        const bool both = c == 0 && joined(b);
+        BatchParams bp = params_of(b, c, both, d_ws, d_out, d_err);
         if (heads) bp.head = reinterpret_cast<uint32_t *>(heads + c * kHeadStride);
         const hipError_t e = launch_batch(bp, t, stream);
         if (e != hipSuccess) return e;
-        if (joined) ++c;
+        if (both) ++c;
     }
     return hipSuccess;
 }
