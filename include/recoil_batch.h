@@ -23,7 +23,7 @@ typedef struct recoil_graph recoil_graph;
 recoil_tuning recoil_default_tuning(void);
 
 /*
- * Plan a batch of `count` blobs (each W = 32 or 64, 8 <= n <= 12). Reports the device
+ * Plan a batch of `count` blobs (each W = 32 or 64, 8 <= n <= 16). Reports the device
  * workspace size (words, tables, unit records, stream descriptors, work items,
  * queue counter) and the output size: stream i's symbols land at the offset given
  * by recoil_batch_output_offset (256-byte aligned). tuning: NULL for the default.
@@ -94,8 +94,8 @@ void recoil_graph_free(recoil_graph *graph);
 
 /*
  * Autotuner: times every launch shape (waves 8/16 x K 4/8 x pairs per wave
- * 1/2/4/8 x units per run 1/2/4/8, shapes that do not fit the CU skipped) on this batch, `reps` timed
- * launches each after one warm-up, keeps the fastest median and leaves it set on
+ * 1/2/4/8 x units per run 0/1/2/4/8, where 0 leaves items and runs to the batch's size;
+ * shapes that do not fit the CU are skipped) on this batch, `reps` timed launches each after one warm-up, keeps the fastest median and leaves it set on
  * the batch (work items re-uploaded). Results are cached per process, keyed by the
  * device architecture and the batch's shape. Synchronises `stream`.
  * best_ms receives the winning median (-1 when served from the cache).

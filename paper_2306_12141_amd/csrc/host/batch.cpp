@@ -573,7 +573,7 @@ recoil_status recoil_autotune(recoil_batch *batch, void *d_ws, void *d_out, uint
         return fail(RECOIL_ERR_HIP, "autotune: event creation failed");
     recoil_tuning best{};
     float best_t = 1e30f;
-    const uint32_t waves_opts[] = {8, 16}, k_opts[] = {4, 8}, p_opts[] = {1, 2, 4, 8}, r_opts[] = {1, 2, 4, 8};
+    const uint32_t waves_opts[] = {8, 16}, k_opts[] = {4, 8}, p_opts[] = {1, 2, 4, 8}, r_opts[] = {0, 1, 2, 4, 8};
     for (uint32_t w : waves_opts)
         for (uint32_t k : k_opts)
             for (uint32_t pp : p_opts)
