@@ -334,7 +334,10 @@ struct PairDecoder {
     // request() reads the records and requests the first chunks, fill() writes them to
     // the ring: two rounds of memory latency, with the loads of both units of a pair and
     // of all chunks in flight together. request() touches no LDS, so the decode table is
-    // staged under the second. Two chunks: the least that leaves C words resident whatever
+    // staged under the second. A launch's last pair may have one run: both half-waves read
+    // its records, and request() is true for the lanes of the lower one only, which decode it
+    // alone (beside a partner without groups it ran predicated to its end: 4099 units of 300
+    // groups 60.1 us, now 40.9; 4098 units 41.2). Two chunks: the least that leaves C words resident whatever
     // the first word's place in its chunk (every wave of the launch asks for them at once,
     // and a third one delays the first group by its share of the bandwidth).
     // Before (a chunk at a time, the units of a pair one after the other, the table
@@ -345,22 +348,18 @@ struct PairDecoder {
         int32_t q0;            // the lane's unit's highest chunk (-1: none)
     };
     __device__ inline bool request(uint32_t pair, First &f) {
-        const uint32_t mine = pair * S + upper;
-        const bool valid = mine < p.runs;
-        const uint32_t lo = valid ? mine * p.run : 0u, hi = valid ? min(lo + p.run, p.units) - 1u : 0u;
-        const bool last = valid && hi + 1 == p.units;
-        const bool full = last || (valid && p.partitioned);   // starts from 32-bit final states
+        const bool valid = S == 1 || pair * S + upper < p.runs;
+        const uint32_t mine = valid ? pair * S + upper : pair * S;
+        const uint32_t lo = mine * p.run, hi = min(lo + p.run, p.units) - 1u;
+        const bool last = hi + 1 == p.units;
+        const bool full = last || p.partitioned;   // starts from 32-bit final states
         UnitMeta m = p.meta[hi];
         m.glo = p.meta[lo].glo;
         rec = p.lanes[(uint64_t)hi * W + coder];
-        if (!valid) {
-            m = UnitMeta{0, 0, 0, 1};
-            rec = 0u;
-        }
         my_top = m.top;
         my_ghi = m.ghi;
-        my_steps = valid && m.top + 1 > m.glo ? m.top + 1 - m.glo : 0u;
-        uint32_t sync = valid ? m.top - m.ghi + 1 : 0u;
+        my_steps = m.top + 1 > m.glo ? m.top + 1 - m.glo : 0u;
+        uint32_t sync = m.top - m.ghi + 1;
         if (full) sync = (last && (p.n_symbols % W)) ? 1u : 0u;   // only the stream's last group is ragged
         x = full ? rec : 0u;
         active = full;
@@ -399,7 +398,7 @@ struct PairDecoder {
         }
 #pragma unroll
         for (int32_t i = 0; i < kFill; ++i) f.c[i] = fetch(max(f.q0 - i, 0));
-        return steps[0] > 0 || (S == 2 && steps[S - 1] > 0);
+        return valid && (steps[0] > 0 || (S == 2 && steps[S - 1] > 0));
     }
     __device__ inline void fill(First &f) {
 #pragma unroll
