@@ -26,7 +26,8 @@ static_assert(sizeof(StreamDesc) == 64, "StreamDesc is 64 bytes");
 // units are decoded in runs of `run` consecutive units (Sec. 3.3; 0 or 1: every
 // split point), and a pair is two runs (W = 32) or one (W = 64, or W = 32 with
 // kItemSingle set in `run`: one unit per wave, the upper half-wave idle, for a
-// stream with no more runs than a workgroup has waves).
+// stream with no more runs than a workgroup has waves, or every stream of a launch
+// whose units take at most half of the chip's wave slots so).
 struct WorkItem {
     uint32_t stream;
     uint32_t first;     // first pair
@@ -66,7 +67,8 @@ constexpr uint32_t kStaticScratchWords = 96, kStaticHeadStride = 32;
 // Device address of that array on the current device, looked up once per device.
 hipError_t static_scratch(uint32_t **ptr);
 
-// Persistent batched launch: queue-head reset kernel + decode kernel on `stream`.
+// Persistent batched launch on `stream`: the decode kernel, and before it, where there are more
+// items than resident workgroups, the kernel that resets the queue head.
 hipError_t launch_batch(const BatchParams &bp, const BatchTuning &t, hipStream_t stream);
 // Occupancy-derived workgroups per CU for a tuning (0 if the tuning is not available),
 // of the kernel for one-level tables or, with wide set, for two-level ones.

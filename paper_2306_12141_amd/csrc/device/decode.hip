@@ -142,9 +142,10 @@ hipError_t launch_units(const DecodeParams &p, const DecodeTuning &t, hipStream_
         // One unit per wave while every run then has a wave of its own on half of
         // the chip's wave slots: the pair kernel would leave half of those waves
         // idle. Beyond, the pairs (two units per instruction) are worth more than
-        // the waves: 8192 units at W = 32, 64 MiB of bytes 50.4 us one by one and
-        // 45.0 us in pairs, 32 Mi 16-bit symbols 34.8 and 29.0, n = 16 68 and 57;
-        // 3000 units 87.8 and 86.5.
+        // the waves. Units of 300 groups, one by one (in 16-wave workgroups) and in
+        // pairs: 4096 of bytes 40.5 us one by one, 4098 in pairs 41.2, 4200 60.9 and
+        // 46.7, 8192 63.2 and 51.8; 4200 of 16-bit symbols 65.8 and 53.0, at n = 16
+        // 84.9 and 63.2.
         const uint32_t rs = resident_blocks<32, Sym, K, WAVES, 1, VAR>(p, t);
         const uint64_t slots = std::min<uint64_t>((uint64_t)rs * WAVES, (uint64_t)kSingleWaves * device_cus());
         const uint32_t k = t.units_per_run && !p.partitioned ? std::min(t.units_per_run, std::max(p.units, 1u)) : 1u;

@@ -18,8 +18,9 @@
 // word w lives at slot w mod 3C, and positions down to -C read the mirror.
 //
 // Per group the scalar unit only advances the LDS address of the unit's next
-// word by twice the number of reading lanes (one s_bcnt1 and one s_lshl1_add
-// per unit); the per-group store offsets are immediates of the unrolled
+// word by twice the number of reading lanes (one s_bcnt1 and one s_lshl1_add;
+// a pair of W = 32 units keeps each unit's address, in words, in its half-wave's
+// lanes instead); the per-group store offsets are immediates of the unrolled
 // super-step.
 //
 // Synchronisation (Sec. 4.1.1): lane j is switched on with its recorded 16-bit
@@ -132,14 +133,6 @@ struct Lds {
 };
 
 __device__ inline uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// (x << 1) + y on the scalar unit in one instruction; the compiler emits a
-// shift and an add for it.
-__device__ inline uint32_t s_lshl1_add(uint32_t x, uint32_t y) {
-    uint32_t r;
-    asm("s_lshl1_add_u32 %0, %1, %2" : "=s"(r) : "s"(x), "s"(y) : "scc");
-    return r;
-}
 
 // Wave issue priority 0..3 (larger values go first; the level is clamped).
 __device__ inline void set_priority(uint32_t level) {
@@ -660,17 +653,14 @@ struct PairDecoder {
         return __ballot(vres < 0) == 0;   // read below the first word: corrupt split data
     }
 
-    // Decodes one pair. left: pairs of the wave's share after this one.
+    // Decodes one pair whose first words have been requested. left: pairs of the wave's share
+    // after this one.
     // The wave's issue priority follows the part of its share still to be
     // decoded (counted in groups with every pair as long as this one, updated
     // every super-step): 3 above one half, 2 above a quarter, 1 above an eighth,
     // else 0. The issue arbiter favours older waves; waves that fall behind are
     // given precedence so that all end together, and the last level, in which
     // the oldest wave goes first again, is kept short.
-    __device__ void run(uint32_t pair, uint32_t left, uint32_t share) {
-        First f;
-        if (request(pair, f)) run(f, left, share);
-    }
     __device__ void run(First &f, uint32_t left, uint32_t share) {
         fill(f);
         uint32_t kmax = 0, kmin = 0xFFFFFFFFu;

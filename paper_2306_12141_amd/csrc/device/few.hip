@@ -20,9 +20,11 @@ using namespace dev;
 
 constexpr uint32_t kLdsBytes = 160u << 10;   // per CU
 // Groups of a run from which super-steps of 16 groups pay: 8-group ones round a run up by
-// less and start sooner (1 MiB at W = 32 in 256 units, 128 groups each: 12.9 against
-// 14.4 us), 16-group ones cost less per group (64 MiB in 256 units, 8192 groups each: 390
-// against 442 us).
+// less and start sooner, 16-group ones cost less per group. 256 runs of bytes at W = 32 with
+// 8- and 16-group super-steps: of 128 groups 10.7 and 11.4 us, 192 14.1 and 13.8, 256 17.2
+// and 16.5, 512 30.4 and 28.3; at n = 16, where a super-step does more, of 128 groups 15.8 and
+// 16.4, 192 21.1 and 21.4, 256 26.6 and 26.6, 512 48.4 and 47.2. One line for both, at what the
+// second needs: one-level tables lose 1 to 4 % between 160 and 255 groups.
 constexpr uint32_t kLongRun = 256;
 constexpr int kRing = 3;                     // chunks of a ring
 
@@ -30,9 +32,10 @@ constexpr int kRing = 3;                     // chunks of a ring
 // workgroups the waves of all runs meet at once, the helpers of 32-lane runs keep half
 // their lanes idle and those of wide tables take two reads per word, so that only 64-lane
 // runs on one-level tables gain (without and with helpers, 64 MiB of bytes or 32 Mi 16-bit
-// symbols: W = 64, 2048 units 58.6 and 55.3 us, 16-bit 37.4 and 36.4 us, n = 16 80.4 and
-// 83.2 us, 1100 units 87.4 and 78.6 us; W = 32, 2048 units 81.5 and 86.5 us, n = 16 131.5
-// and 134.6 us).
+// symbols, four streams in turn: W = 64, 2048 units 56.3 and 52.2 us, 16-bit 39.4 and 38.4 us,
+// 1100 units 86.3 and 76.0 us; one stream: W = 64, n = 16, 2048 units 80.4 and 83.2 us;
+// W = 32, 2048 units 81.5 and 86.5 us, n = 16 131.5 and 134.6 us). A stream that the caches
+// still hold loses a little at the far end: one of 64 MiB in 2048 units 48.0 and 49.9 us.
 constexpr int kShared = 8;
 template <int W, bool WIDE, int WAVES>
 constexpr bool kHelp = WAVES == 1 || (W == 64 && !WIDE);

@@ -18,13 +18,14 @@
 // off the chain, when a chunk is put into the ring: up to one run per SIMD on another
 // wave (HELP), which costs the decoding wave one meeting per super-step.
 //
-// What bounds it: the chain, about 46 ns per group (mad, compare, count, address, select,
-// 8 cycles each for a lone wave, and an LDS read of 44); without a helper the look-ups come
-// on top, 15 ns per group at 0.36 words per symbol. Measured with the throughput kernel (one
-// wave per workgroup), without a helper and with it: 64 MiB of bytes at W = 32 in 256 units
-// 883, 530, 383 us, in 1024 units 225, 138, 117 us; at W = 64 in 256 units 406, 237, 202 us;
-// 1 MiB at W = 32 in 256 units 18.9, 13.6, 11.9 us; 1.5 M 16-bit symbols at W = 64 in 367
-// units 14.7, 10.8, 10.4 us; n = 16, 64 MiB at W = 32 in 256 units 1358, 930, 676 us.
+// What bounds it: the chain, 45.8 ns per group in long runs, 105 to 110 cycles at 2.28 to
+// 2.4 GHz. @CHAIN@ Without a helper the look-ups come on top, 18 ns per group at
+// 0.36 words per symbol.
+// Measured with the throughput kernel of one wave per workgroup, this one without a helper
+// and with it: 64 MiB of bytes at W = 32 in 256 units 885, 524, 376 us, in 1024 units 225,
+// 133, 112 us; at W = 64 in 256 units 405, 236, 201 us; n = 16 at W = 32 in 256 units 1353,
+// 923, 665 us, in 1024 units 330, 211, 174 us; four streams in turn, 1 MiB at W = 32 in 256
+// units 19.2, 12.8, 10.6 us, 1.5 M 16-bit symbols at W = 64 in 367 units 14.9, 9.3, 8.7 us.
 #pragma once
 
 #include "decode_core.hpp"
