@@ -19,8 +19,12 @@
 // wave (HELP), which costs the decoding wave one meeting per super-step.
 //
 // What bounds it: the chain, 45.8 ns per group in long runs, 105 to 110 cycles at 2.28 to
-// 2.4 GHz. @CHAIN@ Without a helper the look-ups come on top, 18 ns per group at
-// 0.36 words per symbol.
+// 2.4 GHz. A lone wave issues in order, a vector instruction 8 cycles after one whose result it
+// takes and about 4 after any other. Eight stand before the LDS read (multiply-add, compare,
+// the table address's two, a wait state, count, word address, select): about 52 cycles; the
+// read takes 44, bank conflicts at most 3 (256 runs of 8192 groups: 6.9 M conflict cycles for 2.1 M
+// groups), the store and the super-step's account and meeting the rest. Without a helper the
+// look-ups come on top, 18 ns per group at 0.36 words per symbol.
 // Measured with the throughput kernel of one wave per workgroup, this one without a helper
 // and with it: 64 MiB of bytes at W = 32 in 256 units 885, 524, 376 us, in 1024 units 225,
 // 133, 112 us; at W = 64 in 256 units 405, 236, 201 us; n = 16 at W = 32 in 256 units 1353,
