@@ -146,11 +146,11 @@ hipError_t launch_units(const DecodeParams &p, const DecodeTuning &t, hipStream_
         // pairs: 4096 of bytes 40.5 us one by one, 4098 in pairs 41.2, 4200 60.9 and
         // 46.7, 8192 63.2 and 51.8; 4200 of 16-bit symbols 65.8 and 53.0, at n = 16
         // 84.9 and 63.2.
-        const uint32_t rs = resident_blocks<32, Sym, K, WAVES, 1, VAR>(p, t);
-        const uint64_t slots = std::min<uint64_t>((uint64_t)rs * WAVES, (uint64_t)kSingleWaves * device_cus());
+        // (The query costs a quarter of a microsecond: only where it can matter.)
         const uint32_t k = t.units_per_run && !p.partitioned ? std::min(t.units_per_run, std::max(p.units, 1u)) : 1u;
         const uint64_t runs = ((uint64_t)p.units + k - 1) / k;
-        if (rs > 0 && runs <= slots) return launch_ss<32, Sym, K, WAVES, 1, VAR>(p, t, rs, stream, shape);
+        const uint32_t rs = runs <= (uint64_t)kSingleWaves * device_cus() ? resident_blocks<32, Sym, K, WAVES, 1, VAR>(p, t) : 0u;
+        if (runs <= (uint64_t)rs * WAVES) return launch_ss<32, Sym, K, WAVES, 1, VAR>(p, t, rs, stream, shape);
     }
     const uint32_t resident = resident_blocks<W, Sym, K, WAVES, 64 / W, VAR>(p, t);
     if (resident == 0) return hipErrorInvalidConfiguration;
