@@ -45,6 +45,11 @@ namespace {
 
 using namespace dev;
 
+// The tuning asked for and the device's compute units, looked up once per launch.
+struct Asked : DecodeTuning {
+    uint32_t cus;
+};
+
 // SS: units per wave. W = 32 runs two units per wave (one per half-wave), or,
 // when the stream has no more units than the grid has waves, one unit per wave
 // with the upper half-wave switched off: then twice as many waves decode.
@@ -107,15 +112,15 @@ int units_occupancy(uint32_t lut_bytes) {
 
 // Resident workgroups of the kernel with SS units per wave (0: does not fit).
 template <int W, typename Sym, int K, int WAVES, int SS, int VAR>
-uint32_t resident_blocks(const DecodeParams &p, const DecodeTuning &t) {
+uint32_t resident_blocks(const DecodeParams &p, const Asked &t) {
     int per_cu = units_occupancy<W, Sym, K, WAVES, SS, VAR>(p.lut_bytes);
     if (per_cu < 1) return 0;
     if (t.blocks_per_cu > 0) per_cu = std::min<int>(per_cu, (int)t.blocks_per_cu);
-    return (uint32_t)(device_cus() * per_cu);
+    return t.cus * (uint32_t)per_cu;
 }
 
 template <int W, typename Sym, int K, int WAVES, int SS, int VAR>
-hipError_t launch_ss(const DecodeParams &p, const DecodeTuning &t, uint32_t resident, hipStream_t stream,
+hipError_t launch_ss(const DecodeParams &p, const Asked &t, uint32_t resident, hipStream_t stream,
                      DecodeShape *shape) {
     DecodeParams q = p;
     q.run = t.units_per_run ? t.units_per_run : auto_units_per_run(p.units, (uint64_t)resident * WAVES * SS);
@@ -137,7 +142,7 @@ hipError_t launch_ss(const DecodeParams &p, const DecodeTuning &t, uint32_t resi
 constexpr uint32_t kSingleWaves = 16;   // waves per CU up to which W = 32 runs are decoded one per wave
 
 template <int W, typename Sym, int K, int WAVES, int VAR>
-hipError_t launch_units(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
+hipError_t launch_units(const DecodeParams &p, const Asked &t, hipStream_t stream, DecodeShape *shape) {
     if constexpr (W == 32) {
         // One unit per wave while every run then has a wave of its own on half of
         // the chip's wave slots: the pair kernel would leave half of those waves
@@ -149,7 +154,7 @@ hipError_t launch_units(const DecodeParams &p, const DecodeTuning &t, hipStream_
         // (The query costs a quarter of a microsecond: only where it can matter.)
         const uint32_t k = t.units_per_run && !p.partitioned ? std::min(t.units_per_run, std::max(p.units, 1u)) : 1u;
         const uint64_t runs = ((uint64_t)p.units + k - 1) / k;
-        const uint32_t rs = runs <= (uint64_t)kSingleWaves * device_cus() ? resident_blocks<32, Sym, K, WAVES, 1, VAR>(p, t) : 0u;
+        const uint32_t rs = runs <= (uint64_t)kSingleWaves * t.cus ? resident_blocks<32, Sym, K, WAVES, 1, VAR>(p, t) : 0u;
         if (runs <= (uint64_t)rs * WAVES) return launch_ss<32, Sym, K, WAVES, 1, VAR>(p, t, rs, stream, shape);
     }
     const uint32_t resident = resident_blocks<W, Sym, K, WAVES, 64 / W, VAR>(p, t);
@@ -160,7 +165,7 @@ hipError_t launch_units(const DecodeParams &p, const DecodeTuning &t, hipStream_
 constexpr uint32_t kSimdsPerCu = 4;
 
 template <int W, typename Sym, int VAR>
-hipError_t launch_fixed(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
+hipError_t launch_fixed(const DecodeParams &p, const Asked &t, hipStream_t stream, DecodeShape *shape) {
     if (t.chunk_groups == 4 && t.waves == 1) return launch_units<W, Sym, 4, 1, VAR>(p, t, stream, shape);
     if (t.chunk_groups == 4 && t.waves == 16) return launch_units<W, Sym, 4, 16, VAR>(p, t, stream, shape);
     if (t.chunk_groups == 4 && t.waves == 8) return launch_units<W, Sym, 4, 8, VAR>(p, t, stream, shape);
@@ -184,9 +189,9 @@ hipError_t launch_fixed(const DecodeParams &p, const DecodeTuning &t, hipStream_
 // the resident workgroups keeps the throughput kernel where waves are asked for, and where
 // they are not if the few-run kernel's grid would exceed it.
 template <int W, typename Sym, int VAR>
-hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_t stream, DecodeShape *shape) {
+hipError_t launch_shape(const DecodeParams &p, const Asked &t, hipStream_t stream, DecodeShape *shape) {
     if (t.waves == 16) return launch_fixed<W, Sym, VAR>(p, t, stream, shape);
-    DecodeTuning u = t;
+    Asked u = t;
     if (t.waves == 0) u.waves = 16;
     DecodeShape s{};
     const hipError_t e = launch_fixed<W, Sym, VAR>(p, u, stream, &s);
@@ -195,7 +200,7 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
         DecodeParams q = p;
         q.run = s.units_per_run;
         q.runs = s.runs;
-        FewShape few{};
+        FewShape few{t.cus, 0, 0};
         hipError_t fe = hipSuccess;
         if (decode_few(q, W, sizeof(Sym), t.waves, t.blocks_per_cu, few, shape == nullptr, stream, &fe)) {
             if (shape) *shape = DecodeShape{few.blocks, few.waves, s.units_per_run, s.runs, 1u};
@@ -204,9 +209,8 @@ hipError_t launch_shape(const DecodeParams &p, const DecodeTuning &t, hipStream_
     }
     if (t.waves == 0) {
         const uint64_t pieces = s.units_per_wave ? (s.runs + s.units_per_wave - 1) / s.units_per_wave : 0;
-        const uint64_t cus = (uint64_t)device_cus();
-        if (pieces <= kSimdsPerCu * cus) u.waves = 1;
-        else if (pieces < 16 * cus) u.waves = 8;
+        if (pieces <= (uint64_t)kSimdsPerCu * t.cus) u.waves = 1;
+        else if (pieces < (uint64_t)16 * t.cus) u.waves = 8;
     }
     return launch_fixed<W, Sym, VAR>(p, u, stream, shape);
 }
@@ -228,7 +232,7 @@ int device_cus() {
     return cus;
 }
 
-hipError_t launch_decode(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, const DecodeTuning &t,
+hipError_t launch_decode(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, const DecodeTuning &tuning,
                          hipStream_t stream, DecodeShape *shape) {
     if (shape) *shape = DecodeShape{0, 0, 0, 0, 0};
     if (p.n_symbols == 0) return hipSuccess;
@@ -244,6 +248,7 @@ hipError_t launch_decode(const DecodeParams &p, uint32_t lanes, uint32_t symbol_
         return hipGetLastError();
     }
     if (p.lut_bytes % 16 || p.lut_bytes > kMaxTableBytes) return hipErrorInvalidValue;
+    const Asked t{tuning, (uint32_t)device_cus()};
     if (p.quant_bits > 12) {
         // Wide tables (two-level, 13 <= n <= 16): plain decoding only.
         if (p.counts || p.tidx) return hipErrorInvalidValue;

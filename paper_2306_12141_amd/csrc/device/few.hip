@@ -19,6 +19,7 @@ namespace {
 using namespace dev;
 
 constexpr uint32_t kLdsBytes = 160u << 10;   // per CU
+constexpr uint32_t kSimds = 4;               // per CU
 // Groups of a run from which super-steps of 16 groups pay: 8-group ones round a run up by
 // less and start sooner, 16-group ones cost less per group. 256 runs of bytes at W = 32 with
 // 8- and 16-group super-steps: of 128 groups 10.7 and 11.4 us, 192 14.1 and 13.8, 256 17.2
@@ -100,7 +101,7 @@ __global__ __launch_bounds__((kThreads<W, WIDE, WAVES>)) void decode_few_runs(De
 template <int W, typename Sym, int K, bool WIDE, bool COUNT, int WAVES>
 bool try_launch(const DecodeParams &p, const FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
     const uint32_t lds = table_bytes<Sym, WIDE>(p.lut_bytes) + WAVES * FewDecoder<W, Sym, K, kRing, WIDE, COUNT, kHelp<W, WIDE, WAVES>>::RING_BYTES;
-    const uint32_t cus = (uint32_t)device_cus(), per_cu = (shape.blocks + cus - 1) / cus;
+    const uint32_t per_cu = (shape.blocks + shape.cus - 1) / shape.cus;
     if (lds * per_cu > kLdsBytes) return false;
     if (launch) {
         hipLaunchKernelGGL((decode_few_runs<W, Sym, K, WIDE, COUNT, WAVES>), dim3(shape.blocks), dim3((kThreads<W, WIDE, WAVES>)), lds,
@@ -138,13 +139,12 @@ bool pick_variant(const DecodeParams &p, const FewShape &shape, bool launch, hip
 
 bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, uint32_t waves, uint32_t blocks_per_cu,
                 FewShape &shape, bool launch, hipStream_t stream, hipError_t *e) {
-    constexpr uint32_t kSimds = 4;   // per CU
-    const uint32_t cus = (uint32_t)device_cus();
+    const uint32_t cus = shape.cus;
     // Two runs per SIMD still run at almost the pace of one (64 MiB at W = 32 in 2048 units:
     // 117 us with the throughput kernel, 82 us here); four do not (4096 units: 70 against
     // 73 us, the rings are then down to 4 groups).
     if (p.tidx || p.runs == 0 || p.runs > 2 * kSimds * cus) return false;
-    shape = p.runs <= kSimds * cus ? FewShape{p.runs, 1} : FewShape{cus, (uint32_t)kShared};
+    shape = p.runs <= kSimds * cus ? FewShape{cus, p.runs, 1} : FewShape{cus, cus, (uint32_t)kShared};
     if (waves && waves != shape.waves) return false;
     // Every run is resident from the start, so a cap below that is left to the throughput
     // kernel, whose workgroups decode one run after another.

@@ -6,6 +6,7 @@
 namespace recoil {
 
 struct FewShape {
+    uint32_t cus;             // the device's compute units (set by the caller)
     uint32_t blocks, waves;   // workgroups, decoding waves of each
 };
 
