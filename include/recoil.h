@@ -118,7 +118,8 @@ typedef struct {
  *                  when 16-wave workgroups would not reach every CU, so that the
  *                  waves spread over all CUs. With 0, 1 and 8 a decode of at most
  *                  two runs per SIMD goes to a kernel of its own (at most one: 1 wave
- *                  decodes per workgroup; above: 8)
+ *                  decodes per workgroup; above: 8, and with 0 only runs that are long
+ *                  enough for it, of up to 112 symbol groups by symbol size, W and n)
  *   chunk_groups   K (4 or 8): symbol groups per super-step; each unit's LDS bitstream
  *                  ring holds 4 K W words (3 K W ring + K W mirror). The kernel for few
  *                  runs chooses its own (4, 8 or 16)

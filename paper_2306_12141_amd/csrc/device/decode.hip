@@ -183,7 +183,8 @@ hipError_t launch_fixed(const DecodeParams &p, const Asked &t, hipStream_t strea
 // of a few CUs and leaves the rest idle, while each wave's decode is one
 // latency-bound chain that runs faster with fewer waves beside it. Up to two runs per
 // SIMD the kernel of few.hip decodes it, whose chain is half as long (its 8-byte table
-// and ring entries leave no room in the LDS for more): also where one or eight waves
+// and ring entries leave no room in the LDS for more), except runs above one per SIMD
+// that are too short for its start: also where one or eight waves
 // are asked for and that is the shape it takes, so that a tuned plan is not left with
 // the slower kernel (64 MiB at W = 32 in 256 units, waves = 1: 883 against 383 us). A cap on
 // the resident workgroups keeps the throughput kernel where waves are asked for, and where

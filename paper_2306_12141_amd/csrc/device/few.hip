@@ -135,6 +135,26 @@ bool pick_variant(const DecodeParams &p, const FewShape &shape, bool launch, hip
                     : pick_waves<W, Sym, false, false>(p, shape, launch, stream, e);
 }
 
+// Groups of a run from which shared workgroups pay where the shape is left open: a CU's eight
+// rings and its table are filled before the first group, so a short run is faster on the
+// throughput kernel. Time against that kernel's (replayed graphs, streams in turn):
+//   bytes, W = 64     2048 runs of 24, 48, 72, 128 groups 1.21, 1.07, 0.99, 0.93; 1500 runs 1.09,
+//                     1.02, 0.95, 0.87; 1100 runs 1.00, 0.94, 0.90, 0.84
+//   16-bit, W = 64    2048 runs 1.23, 1.03, 0.99, 0.95; 1100 runs 1.11, 0.98, 0.91, 0.86
+//   16-bit, W = 32    2048 runs 1.13, 1.09, 1.01, 0.99; 1100 runs 1.05, 0.99, 0.98, 0.97
+//   n = 16, W = 32    2048 runs of 24, 72, 112, 160 groups 1.17, 1.08, 1.03, 0.97; 1100 runs 1.07,
+//                     1.01, 0.98, 0.95
+//   n = 16, bytes, W = 64  2048 runs 1.30, 1.09, 1.01, 0.98; 1100 runs 1.10, 1.05, 1.00, 0.95
+//   n = 16, 16-bit, W = 64 2048 runs of 24, 56, 72 groups 1.07, 0.99, 0.99; 1100 runs 0.97 to 1.02
+// Bytes at W = 32 gain or break even (2048 runs of 10 groups 1.03, of 72 0.97, 1100 runs 0.97 and
+// 0.88). few_more: at most an eighth more runs than SIMDs.
+uint32_t shared_from(uint32_t lanes, uint32_t symbol_bytes, bool wide, bool few_more) {
+    if (wide && lanes == 32) return few_more ? 88 : 112;
+    if (wide) return symbol_bytes == 1 ? (few_more ? 56 : 112) : few_more ? 0 : 56;
+    if (symbol_bytes == 1) return lanes == 32 ? (few_more ? 0 : 16) : few_more ? 24 : 64;
+    return lanes == 32 ? (few_more ? 72 : 88) : few_more ? 48 : 64;
+}
+
 }  // namespace
 
 bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, uint32_t waves, uint32_t blocks_per_cu,
@@ -149,6 +169,9 @@ bool decode_few(const DecodeParams &p, uint32_t lanes, uint32_t symbol_bytes, ui
     // Every run is resident from the start, so a cap below that is left to the throughput
     // kernel, whose workgroups decode one run after another.
     if (blocks_per_cu && (shape.blocks + cus - 1) / cus > blocks_per_cu) return false;
+    if (waves == 0 && shape.waves > 1 &&
+        p.n_symbols / lanes / p.runs < shared_from(lanes, symbol_bytes, p.quant_bits > 12, p.runs <= kSimds * cus * 9 / 8))
+        return false;
     static_assert(kShared == 2 * kSimds, "a workgroup per CU holds two runs per SIMD");
     if (lanes == 32) return symbol_bytes == 1 ? pick_variant<32, uint8_t>(p, shape, launch, stream, e)
                                               : pick_variant<32, uint16_t>(p, shape, launch, stream, e);
