@@ -322,7 +322,9 @@ recoil_status recoil_plan_decode_table(const recoil_plan *plan, void *dst, size_
  * Errors: INVALID_ARG (unsupported shape). */
 recoil_status recoil_plan_set_tuning(recoil_plan *plan, const recoil_tuning *tuning);
 /* Autotuner for one plan: times every launch shape (waves per workgroup 1/8/16 x
- * K 4/8 x units per run 0/1/2/4) with recoil_decode on the caller's buffers,
+ * K 4/8 x units per run 0/1/2/4; for few runs 1 and 8 also with a blocks_per_cu
+ * that caps nothing but keeps the decode on the throughput kernel) with
+ * recoil_decode on the caller's buffers,
  * `reps` timed launches each after one warm-up, keeps the fastest median and
  * leaves it set on the plan. Results are cached per process, keyed by the
  * device architecture and the stream's shape (N, M, W, symbol bytes, n).

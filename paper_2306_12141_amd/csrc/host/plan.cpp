@@ -577,10 +577,16 @@ recoil_status recoil_plan_autotune(recoil_plan *plan, void *d_ws, void *d_out, u
     DecodeTuning best = saved;
     float best_t = 1e30f;
     const uint32_t waves_opts[] = {1, 8, 16}, k_opts[] = {4, 8}, run_opts[] = {0, 1, 2, 4};
+    // One or eight waves also with a cap that no launch reaches (32 waves per CU): where the
+    // few-run kernel takes the uncapped shape, that is the throughput kernel's, the faster
+    // one for short runs (2048 runs of 24 groups at W = 64: 7.2 against 8.6 us).
+    const uint64_t few = 8ull * (uint64_t)device_cus();
     for (uint32_t w : waves_opts)
         for (uint32_t k : k_opts)
-            for (uint32_t r : run_opts) {
-                pl.tuning = DecodeTuning{w, k, 0, r};
+            for (uint32_t r : run_opts)
+            for (uint32_t cap : {0u, 32u / w}) {
+                if (cap && (w == 16 || (pl.units + std::max(r, 1u) - 1) / std::max(r, 1u) > few)) continue;
+                pl.tuning = DecodeTuning{w, k, cap, r};
                 // One warm-up launch, then the median of `reps` timed launches.
                 if (recoil_decode(plan, d_ws, d_out, d_error, stream)) continue;
                 std::vector<float> ts;
