@@ -84,7 +84,7 @@ recoil_status recoil_decode_batch_noalloc(const recoil_batch *batch, const void 
 recoil_status recoil_decode_batch_per_stream(const recoil_batch *batch, const void *d_workspace, void *d_out,
                                              uint32_t *d_error, hipStream_t stream);
 
-/* Capture the [queue reset; persistent decode] pair of every class for these buffers in a HIP graph
+/* Capture the launches of recoil_decode_batch for these buffers in a HIP graph
  * (captured on a private stream) and instantiate it. Replay with recoil_graph_launch.
  * Errors: INVALID_ARG, HIP. */
 recoil_status recoil_batch_graph_create(const recoil_batch *batch, void *d_workspace, void *d_out, uint32_t *d_error,

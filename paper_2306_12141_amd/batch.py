@@ -110,7 +110,7 @@ class Batch:
 
 
 class Graph:
-    """An instantiated HIP graph of [queue reset; persistent batched decode]."""
+    """An instantiated HIP graph of a batch's decode launches."""
 
     def __init__(self, handle):
         self._h = handle
